@@ -32,7 +32,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "decode tokens/s at 1 GPU; % of H2D-link roofline; GPU-busy %"
-KERNEL_SOURCES = ("gemm.hip", "attention.hip", "device.h")
+KERNEL_SOURCES = ("gemm.hip", "gemm_slab.h", "gemm_common.h", "attention.hip", "device.h")
 HBM_PEAK_GBPS = 8000.0
 MFMA_F16_PEAK_TFLOPS = 2500.0
 
@@ -70,45 +70,60 @@ def parse():
     return ap.parse_args()
 
 
-# the decode GEMM kernel plan of gemm.hip, restated to name the kernels in
-# rocprofv3 output: (NF, KW, PD, KC) of the streaming kernel by (INT4, MF)
-_STREAM_SEL = {(False, 2): (1, 8, 2, 128), (False, 4): (1, 8, 2, 128), (False, 8): (1, 8, 2, 128),
-               (True, 2): (1, 8, 2, 256), (True, 4): (2, 8, 4, 256), (True, 8): (2, 8, 4, 128)}
-
-
 def gemm_family(M):
-    return "gemm_skinny" if M <= 16 else ("gemm_stream" if M <= 128 else "gemm_tiled")
+    return "gemm_skinny" if M <= 16 else ("gemm_slab" if M <= 128 else "gemm_prefill")
+
+
+def _split_k(wgs, K, kper_min):
+    S = 1
+    while S < 8 and wgs * 2 * S <= 256 and K % (2 * S * 128) == 0 and K // (2 * S) >= kper_min:
+        S *= 2
+    return S
 
 
 def gemm_symbols(M, N, K, epi, w4, frag):
-    """Kernel symbols one GEMM launches: skinny (M <= 16; 64 W rows per
-    workgroup when N >= 12288), streaming (16 < M <= 128; K split into the
-    largest power of two <= 8 keeping the grid within 256 workgroups, plus
-    its combine kernel), tiled, or big tiles (at least 512 tiles of
-    256 x 256); `frag`: W in fragment order."""
+    """Kernel symbols one decode GEMM (M <= 128) launches, the plan of
+    gemm.hip restated to name the kernels in rocprofv3 output: skinny, or a
+    slab configuration (MF, NF, WN, KS, PD) and, with several K ranges, the
+    merge kernel; `frag`: W in fragment order."""
     b = "true" if w4 else "false"
     pk = "true" if frag else "false"
-    if M <= 16:
-        # (the SwiGLU epilogue, 5, always pairs two gate and two up fragments)
-        nf = 4 if N >= 64 * 192 or epi == 5 else 1
-        return [f"gemm_skinny<{nf}, 1, 8, 2, {b}, {epi}, {pk}>(GemmArgs)"]
-    if -(-M // 256) * -(-N // 256) >= 512:
-        return [f"gemm_big_w4<{epi}, {pk}>(GemmArgs)" if w4 else f"gemm_big_f16<{epi}, {pk}>(GemmArgs)"]
     if M > 128:
-        return [f"gemm_tiled<{b}, {epi}, {pk}>(GemmArgs)"]
-    mf = 2 if M <= 32 else (4 if M <= 64 else 8)
-    nf, kw, pd, kc = _STREAM_SEL[(w4, mf)]
-    if K % kc:
-        pd, kc = (pd if kc == 128 else 2 * pd), 128
-    blocks = -(-N // (16 * nf * kw))
+        raise ValueError("decode GEMMs only")
     S = 1
-    while S < 8 and blocks * 2 * S <= 256 and K % (2 * S * kc) == 0:
-        S *= 2
-    # fp16 grids left under 192 workgroups unsplit take 6 waves per workgroup
-    if not w4 and kc == _STREAM_SEL[(w4, mf)][3] and S == 1 and blocks < 192 \
-            and -(-N // (16 * nf * 6)) <= 256:
-        kw = 6
-    syms = [f"gemm_stream<{nf}, {mf}, {kw}, {pd}, {b}, {kc}, {epi}, {pk}>(GemmArgs, float*, long)"]
+    if M <= 16:
+        cfg = None
+        if epi != 5 and not (w4 and epi == 0):   # (always the skinny kernel)
+            if 5120 <= N <= 8192 and (M > 8 or (not w4 and K >= 16384)):
+                cfg = (1, 2, 1, 8, 4) if w4 else (1, 2, 1, 8, 2)
+            elif N < 5120 and M > 8 and not w4:
+                cfg = (1, 1, 1, 8, 3)
+        if cfg is None:
+            nf = 4 if N >= 64 * 192 or epi == 5 else 1
+            return [f"gemm_skinny<{nf}, 1, 8, 2, {b}, {epi}, {pk}>(GemmArgs)"]
+    else:
+        mf = 2 if M <= 32 else (4 if M <= 64 else 8)
+        if w4:
+            narrow = N <= 16384 and K < {2: 14336, 4: 16384, 8: 8193}[mf]
+            cfg = {(2, True): (2, 2, 2, 4, 3), (2, False): (2, 2, 4, 4, 2),
+                   (4, True): (4, 2, 2, 4, 2), (4, False): (4, 4, 2, 4, 2),
+                   (8, True): (8, 2, 2, 4, 1), (8, False): (8, 2, 4, 2, 2)}[mf, narrow]
+        elif mf == 2:
+            cfg = ((2, 1, 2, 4, 3) if N <= 8192 and K <= 8192 else
+                   (2, 3, 2, 2, 3) if 8192 < N <= 24576 else (2, 2, 4, 2, 2))
+        elif mf == 4 and 16384 < N <= 24576:
+            cfg = (4, 3, 2, 2, 2)
+        else:
+            narrow = N <= 16384 and K < {4: 16384, 8: 6145}[mf]
+            cfg = {(4, True): (4, 1, 4, 2, 3), (4, False): (4, 1, 8, 1, 3),
+                   (8, True): (8, 1, 4, 2, 2), (8, False): (8, 1, 8, 1, 3)}[mf, narrow]
+        if K >= 1536:
+            S = _split_k(-(-N // (16 * cfg[1] * cfg[2])), K, 256)
+    args = ", ".join(str(v) for v in cfg)
+    syms = [f"gemm_slab<{args}, {b}, {epi}, {pk}>(GemmArgs, float*, long)"]
+    if w4 and not frag and cfg == (2, 2, 4, 4, 2):    # row-major INT4: the streaming kernel
+        pd, kc = (2, 256) if K % (256 * S) == 0 else (4, 128)
+        syms = [f"gemm_stream_w4<{pd}, {kc}, {epi}>(GemmArgs, float*, long)"]
     if S > 1:
         # four columns per thread when N allows (the engine's partials are aligned)
         syms.append(f"gemm_combine<{epi}, {S}, {4 if N % 4 == 0 else 1}>(GemmArgs, float const*)")

@@ -46,14 +46,15 @@ enum { PIPO_EPI_F16 = 0, PIPO_EPI_RELU_F16 = 1, PIPO_EPI_ADD_F32 = 2, PIPO_EPI_F
  * (row stride N), fp16 or fp32 per epilogue ([M][N/2] fp16 for
  * PIPO_EPI_SWIGLU).  K must be a multiple of 128 and M below 2^31 (else
  * PIPO_ERR_UNSUPPORTED).
- * For 16 < M <= 128 the K range may be split over workgroups whose fp32
- * partial sums go to `workspace` (device, caller-owned, contents
- * arbitrary) of pipo_op_gemm_workspace_bytes(M, N, K, wfmt) bytes; a second
- * kernel adds them in a fixed order and applies the epilogue.  With less
- * (or NULL) workspace the GEMM runs unsplit; the result is the same up to
- * rounding.  Calls sharing a workspace must not overlap in time.  For a
- * given (M, N, K, workspace sufficient or not) the summation order is
- * fixed, so repeated calls give the same bits.
+ * For M > 16 the K range may be split over workgroups whose fp32 partial
+ * sums go to `workspace` (device, caller-owned, contents arbitrary) of
+ * pipo_op_gemm_workspace_bytes(M, N, K, wfmt) bytes; a second kernel adds
+ * them in a fixed order and applies the epilogue.  With less (or NULL)
+ * workspace the GEMM takes as many of its K ranges as fit, or runs unsplit;
+ * the result is the same up to rounding.  Calls sharing a workspace must not
+ * overlap in time.  For a given (M, N, K, wfmt, epilogue) and room in the
+ * workspace the summation order is fixed, so repeated calls give the same
+ * bits.
  */
 pipo_status pipo_op_gemm_f16(const uint16_t* X, const uint16_t* W, const uint16_t* bias,
                              void* out, int64_t M, int64_t N, int64_t K, int32_t epi,

@@ -114,10 +114,10 @@ struct GemmArgs {
 };
 
 // kernel launchers (gemm.hip, attention.hip, elementwise.hip)
-// 16 < M <= 128 may split K over workgroups; their partial sums need
-// `workspace` (gemm_workspace_bytes; contents arbitrary, not shared by
-// overlapping launches).  With less the GEMM runs unsplit, equal up to
-// rounding.  gemm_workspace_bytes_upto covers every M up to M_max.
+// M > 16 may split K over workgroups; their partial sums need `workspace`
+// (gemm_workspace_bytes; contents arbitrary, not shared by overlapping
+// launches).  With less the GEMM takes fewer K ranges, equal up to rounding.
+// gemm_workspace_bytes_upto covers the decode sizes (M <= 128) up to M_max.
 pipo_status launch_gemm(const GemmArgs& a, bool w4, int epi, float* workspace,
                         int64_t workspace_bytes, hipStream_t st);
 int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4);

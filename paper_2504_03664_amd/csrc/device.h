@@ -122,6 +122,31 @@ __device__ __forceinline__ h8 dequant8(uint32_t v, h2 s2, h2 m2) {
   return out;
 }
 
+// eight codes in natural order through the fp8 converter: a byte holding a
+// code c (0..15) reads as the fp8 (e4m3) number c * 2^-9, subnormal up to 7
+// and exact throughout, so one instruction turns two of them into fp16 with
+// the scale 2^9.  Per word: the bytes are spread to 16 bits (two permutes),
+// their two codes to a byte each (shift-or, mask), then four conversions and
+// four fused multiply-adds: 14 instructions and the values of dequant8,
+// where biased halves in natural order took 16.
+__device__ __forceinline__ h8 dequant8_fp8(uint32_t v, h2 s2, h2 m2) {
+  h8 out;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const uint32_t b = __builtin_amdgcn_perm(0u, v, j ? 0x0c030c02u : 0x0c010c00u);
+    const uint32_t c = (b | (b << 4)) & 0x0F0F0F0Fu;
+    const h2 clo = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c, 512.f, false));
+    const h2 chi = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c, 512.f, true));
+    const h2 lo = __builtin_elementwise_fma(clo, s2, m2);
+    const h2 hi = __builtin_elementwise_fma(chi, s2, m2);
+    out[4 * j] = lo[0];
+    out[4 * j + 1] = lo[1];
+    out[4 * j + 2] = hi[0];
+    out[4 * j + 3] = hi[1];
+  }
+  return out;
+}
+
 // eight fp16 values permuted to the order of dequant8_interleaved, so that
 // an MFMA sees matching k on both operands
 __device__ __forceinline__ h8 interleave_h8(h8 x) {
@@ -174,6 +199,16 @@ __device__ __forceinline__ int64_t w4_sm(int64_t n, int64_t k, int64_t K) {
 // be the same for every lane.  Counted by vmcnt like any vector load.
 __device__ __forceinline__ void lds_dma16(const void* g, uint8_t* lds) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+// the same for weights (NT: read once per pass, non-temporal), and 4 bytes
+// per lane
+template <bool NT>
+__device__ __forceinline__ void lds_dma16_w(const void* g, uint8_t* lds) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0,
+                                   NT ? 2 : 0);
+}
+__device__ __forceinline__ void lds_dma4(const void* g, uint8_t* lds) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 4, 0, 0);
 }
 // s_waitcnt immediate: at most `vm` vector memory operations outstanding
 // and, with lgkm0, no LDS operation (vmcnt bits 3:0 and 15:14, expcnt 6:4

@@ -3,95 +3,36 @@
 // with W in fp16 or group-wise INT4 (codes expanded to fp16 in registers,
 // the paper's "compute directly on 4-bit weights", Section 3.4).
 //
-// The kernel is chosen by M (and N and the weight format):
+// The kernel is chosen from the shape (gemm_plan):
 //   * gemm_skinny (M <= 16, decode): every workgroup owns 16 or 64 rows of
 //     W and all M rows of X; its waves split K; W streams from HBM straight
 //     into MFMA operand registers (no LDS), X comes from L2.  Partial sums
 //     are combined across waves in LDS in a fixed order.
-//   * gemm_stream (16 < M <= 128, decode): waves split the rows of W, the
-//     chunk of X that all of them need is staged once per workgroup in LDS,
-//     and each wave keeps several chunks of its W rows in flight in
-//     registers.  K may be split over workgroups; their fp32 partial sums
-//     go to a workspace that gemm_combine adds up in a fixed order.
-//   * gemm_tiled (M > 128, prefill with fewer big tiles): 128 x 128 output tiles, K staged
-//     through double-buffered LDS in steps of 64, 4 waves of 64 x 64; tiles
-//     ordered per XCD so that each XCD's L2 serves a compact block.
-//   * gemm_big_f16 / gemm_big_w4 (prefill with at least 512 tiles of
-//     256 x 256): 8 waves of 128 x 64 fed by global -> LDS loads (no
-//     register staging) through rings of LDS stages; INT4 codes reach LDS
-//     the same way and are expanded there, once per tile.
+//   * gemm_slab (gemm_slab.h; M <= 128, and prefill with few tiles): X shared
+//     through LDS, every W row owned by one wave, all moved by global -> LDS
+//     loads several stages ahead; K split over waves, and over workgroups
+//     whose fp32 partial sums go to a workspace that gemm_combine adds up in
+//     a fixed order.
+//   * gemm_stream_w4 (16 < M <= 32, row-major INT4 W).
+//   * gemm_big_f16 / gemm_big_w4 (prefill with 256 x 256 tiles): 8 waves of
+//     128 x 64 fed by global -> LDS loads through rings of LDS stages; INT4
+//     codes reach LDS the same way and are expanded there, once per tile;
+//     fp16 may split K like gemm_slab.
+//   * gemm_tiled (M > 16, operands that are not 16-byte aligned): 128 x 128
+//     output tiles, K staged through registers into double-buffered LDS in
+//     steps of 64, 4 waves of 64 x 64; tiles ordered per XCD so that each
+//     XCD's L2 serves a compact block.
 // The decode kernels read each weight once per pass and do so with
 // non-temporal loads.
 // All accumulate in fp32 with v_mfma_f32_16x16x32_f16, and INT4 codes
 // become the same fp16 values (code * scale + min, rounded once) in every
-// kernel.  The kernel, its configuration and the K split depend only on
-// (M, N, K), so a given shape always sums in the same order; no workgroup
-// reads another workgroup's results within a launch.
-#include "common.h"
-#include "device.h"
+// kernel.  The kernel, its configuration and the K ranges depend only on
+// (M, N, K), the weight format and layout and the workspace, so a given call
+// always sums in the same order; no workgroup reads another workgroup's
+// results within a launch.
+#include "gemm_common.h"
 
 namespace pipo {
-
-// Epilogue, split into what depends on the output row only (its offsets,
-// computed once per row by kernels that own many columns of it) and the
-// per-element part.  EPI_QKV: row m is sequence m / rows_per_seq at
-// position pos0 + m % rows_per_seq, whose k and v go to cache row
-// position * batch + sequence.
-struct EpiRow {
-  int64_t m;      // output row (>= M: none)
-  int64_t off;    // m * ldo, or m * d for q (EPI_QKV)
-  int64_t kvoff;  // EPI_QKV: cache row * dkv
-};
-
-template <int EPI>
-__device__ __forceinline__ EpiRow epilogue_row(const GemmArgs& a, int64_t m) {
-  EpiRow r{m, 0, 0};
-  if (m >= a.M) return r;
-  if constexpr (EPI == EPI_QKV) {
-    // launch_gemm keeps M below 2^31, so 32-bit division is exact
-    const uint32_t mm = (uint32_t)m, rps = (uint32_t)a.rows_per_seq;
-    const uint32_t seq = mm / rps;
-    const int64_t pos = a.pos0 + (int64_t)(mm - seq * rps);
-    r.off = m * a.d;
-    r.kvoff = (pos * a.batch + seq) * a.dkv;
-  } else {
-    r.off = m * a.ldo;
-  }
-  return r;
-}
-
-// bias of column n (0 past N or without bias)
-__device__ __forceinline__ float epilogue_bias(const GemmArgs& a, int64_t n) {
-  return (a.bias && n < a.N) ? h2f(a.bias[n]) : 0.f;
-}
-
-// v: the sum with the column's bias added
-template <int EPI>
-__device__ __forceinline__ void epilogue_store(const GemmArgs& a, const EpiRow& r, int64_t n,
-                                               float v) {
-  if (r.m >= a.M || n >= a.N) return;
-  if constexpr (EPI == EPI_F16) {
-    a.out16[r.off + n] = f2h(v);
-  } else if constexpr (EPI == EPI_RELU_F16) {
-    a.out16[r.off + n] = f2h(v > 0.f ? v : 0.f);
-  } else if constexpr (EPI == EPI_ADD_F32) {
-    a.out32[r.off + n] += v;
-  } else if constexpr (EPI == EPI_F32) {
-    a.out32[r.off + n] = v;
-  } else {  // EPI_QKV
-    if (n < a.d)
-      a.q_out[r.off + n] = f2h(v * a.q_scale);
-    else if (n < a.d + a.dkv)
-      a.k_out[r.kvoff + (n - a.d)] = f2h(v);
-    else
-      a.v_out[r.kvoff + (n - a.d - a.dkv)] = f2h(v);
-  }
-}
-
-template <int EPI>
-__device__ __forceinline__ void epilogue(const GemmArgs& a, int64_t m, int64_t n, float acc) {
-  epilogue_store<EPI>(a, epilogue_row<EPI>(a, m), n, acc + epilogue_bias(a, n));
-}
 
 // ---------------------------------------------------------------------------
 // skinny GEMM (decode)
@@ -241,163 +182,95 @@ __global__ __launch_bounds__(KW * 64) void gemm_skinny(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// streaming GEMM (decode at 16 < M <= 128)
+// streaming GEMM (row-major INT4 W, 16 < M <= 32)
 //
-// Workgroup = KW waves; wave w owns W rows n0 + 16 NF w .. + 16 NF and the
+// Workgroup = 8 waves; wave w owns W rows n0 + 16 w .. + 15 and the
 // workgroup covers k in [z kper, (z + 1) kper), z = blockIdx.y.  K is walked
-// in chunks of KC: the X chunk (16 MF rows x KC) is loaded once per
-// workgroup, PD chunks ahead into registers and then into one of two LDS
-// buffers, one barrier per chunk; each wave holds PD chunks of its W rows
-// in registers, refilling a chunk's registers as soon as its MFMAs are
-// issued.  (With X loaded only one chunk ahead, every chunk waited for an
-// L2 round trip before its barrier.)  Every load is unconditional (row and
-// chunk indexes are clamped: rows past M or N are computed and never
-// stored, a clamped chunk is loaded again and not used), which keeps the
-// compiler's wait counts exact so that the prefetch really stays in flight.
-// In a chunk, lane (r, g) feeds MFMA i with W row 16 f + r at
-// k = 32 i + 8 g (fp16) or k = 32 g + 8 i (INT4: 32 consecutive codes per
-// lane, expanded in interleaved order, X permuted to match).
-template <int NF, int MF, int KW, int PD, bool W4, int KC>
-struct StreamCfg {
-  static constexpr int kXRows = 16 * MF;
-  static constexpr int kXLd = KC + 8;  // halves per LDS row (padding against bank conflicts)
-  static constexpr int kThreads = KW * 64;
-  static constexpr int kXH8 = kXRows * KC / 8;                       // 8-half pieces per X chunk
-  static constexpr int kXPerThread = (kXH8 + kThreads - 1) / kThreads;
-  static constexpr int kWRegs = W4 ? KC / 128 : KC / 32;             // u32x4 per W row per chunk
-  static constexpr int kRowsPerWG = 16 * NF * KW;
-};
+// in chunks of KC: the X chunk (32 rows x KC) is loaded once per workgroup,
+// PD chunks ahead into registers and then into one of two LDS buffers, one
+// barrier per chunk; each wave holds PD chunks of its W rows in registers,
+// refilling a chunk's registers as soon as its MFMAs are issued.  Every load
+// is unconditional (row and chunk indexes are clamped: rows past M or N are
+// computed and never stored, a clamped chunk is loaded again and not used),
+// which keeps the compiler's wait counts exact so that the prefetch really
+// stays in flight.  In a chunk, lane (r, g) feeds MFMA i with W row r at
+// k = 32 g + 8 i (32 consecutive codes per lane, expanded in interleaved
+// order, X permuted to match).  It reads 64 or 128 consecutive bytes of a
+// row of codes at a time, where the slab kernel reads 32: at M = 20, N x K =
+// 7168 x 28672, 50 against 62 us.
+constexpr int kStreamKW = 8, kStreamRows = 16 * kStreamKW;
 
 __device__ __forceinline__ int64_t clamp_hi(int64_t v, int64_t hi) { return v < hi ? v : hi; }
 
-template <int NF, int MF, int KW, int PD, bool W4, int KC, int EPI, bool PK>
-__global__ __launch_bounds__(KW * 64) void gemm_stream(GemmArgs a, float* part, int64_t kper) {
-  using C = StreamCfg<NF, MF, KW, PD, W4, KC>;
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][C::kXRows * C::kXLd];
+template <int PD, int KC, int EPI>
+__global__ __launch_bounds__(kStreamKW * 64) void gemm_stream_w4(GemmArgs a, float* part,
+                                                                 int64_t kper) {
+  constexpr int MF = 2, kThreads = kStreamKW * 64;
+  constexpr int kXLd = KC + 8;  // halves per LDS row (padding against bank conflicts)
+  constexpr int kXPerThread = 16 * MF * KC / 8 / kThreads;  // 8-half pieces of an X chunk
+  static_assert(kXPerThread * kThreads * 8 == 16 * MF * KC, "X pieces split evenly");
+  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][16 * MF * kXLd];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int64_t nw0 = ((int64_t)blockIdx.x * KW + wave) * (16 * NF);
+  const int64_t nw0 = ((int64_t)blockIdx.x * kStreamKW + wave) * 16;
   const int64_t kbeg = (int64_t)blockIdx.y * kper;
   const int64_t nch = kper / KC;
   const int64_t K = a.K;
-  int64_t wrow[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) wrow[f] = clamp_hi(nw0 + 16 * f + r, a.N - 1);
+  const int64_t wrow = clamp_hi(nw0 + r, a.N - 1);
 
   struct WChunk {
-    u32x4 w[NF][C::kWRegs];
-    uint32_t sm[NF][W4 ? KC / 128 : 1];
+    u32x4 w[KC / 128];
+    uint32_t sm[KC / 128];
   };
-  // Fragment order: a lane's 16 bytes of a 16-row block sit at the same
-  // offset in every block of its row group, and the blocks of a row group
-  // follow each other along k, so a lane's address is its own base plus a
-  // workgroup-uniform block offset (fp16: 32-k blocks of 1 KiB; INT4:
-  // 128-k blocks of 1 KiB of codes and 32 (scale, min) words).
-  const uint8_t* wlane[NF];
-  const uint32_t* smlane[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    const int64_t grp = wrow[f] >> 4;
-    if constexpr (W4) {
-      wlane[f] = a.Wq + grp * (K >> 7) * 1024 + (((wrow[f] & 15) + 16 * g) << 4);
-      smlane[f] = reinterpret_cast<const uint32_t*>(a.Wsm) + grp * (K >> 7) * 32 +
-                  (wrow[f] & 15) * 2 + (g >> 1);
-    } else {
-      wlane[f] = reinterpret_cast<const uint8_t*>(a.W) + grp * (K >> 5) * 1024 +
-                 (((wrow[f] & 15) + 16 * g) << 4);
-      smlane[f] = nullptr;
-    }
-  }
   const auto load_w = [&](WChunk& F, int64_t c) {
     const int64_t k0 = kbeg + clamp_hi(c, nch - 1) * KC;
-    if constexpr (PK) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        if constexpr (W4) {
-#pragma unroll
-          for (int t = 0; t < KC / 128; ++t) {
-            const int64_t blk = (k0 >> 7) + t;
-            F.w[f][t] = load_u32x4_stream(wlane[f] + blk * 1024);
-            F.sm[f][t] = smlane[f][blk * 32];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < C::kWRegs; ++i)
-            F.w[f][i] = load_u32x4_stream(wlane[f] + ((k0 >> 5) + i) * 1024);
-        }
-      }
-      return;
-    }
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      if constexpr (W4) {
-#pragma unroll
-        for (int t = 0; t < KC / 128; ++t) {
-          const int64_t kb = k0 + 128 * t + 32 * g;
-          F.w[f][t] = load_u32x4_stream(a.Wq + w4_byte<PK>(wrow[f], kb, K));
-          F.sm[f][t] = *reinterpret_cast<const uint32_t*>(a.Wsm + w4_sm<PK>(wrow[f], kb, K) * 2);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < C::kWRegs; ++i)
-          F.w[f][i] = load_u32x4_stream(a.W + w16_index<PK>(wrow[f], k0 + 32 * i + 8 * g, K));
-      }
+    for (int t = 0; t < KC / 128; ++t) {
+      const int64_t kb = k0 + 128 * t + 32 * g;
+      F.w[t] = load_u32x4_stream(a.Wq + w4_byte<false>(wrow, kb, K));
+      F.sm[t] = *reinterpret_cast<const uint32_t*>(a.Wsm + w4_sm<false>(wrow, kb, K) * 2);
     }
   };
   // X chunks travel through registers PD chunks ahead of their use, like W:
   // chunk c sits in ring slot c % PD from its load (iteration c - 1 - PD)
   // until it is stored to LDS (end of iteration c - 1)
-  h8 xr[PD][C::kXPerThread];
+  h8 xr[PD][kXPerThread];
   const auto load_x = [&](int slot, int64_t c) {
     const int64_t k0 = kbeg + clamp_hi(c, nch - 1) * KC;
 #pragma unroll
-    for (int j = 0; j < C::kXPerThread; ++j) {
-      const int e = tid + j * C::kThreads < C::kXH8 ? tid + j * C::kThreads : C::kXH8 - 1;
+    for (int j = 0; j < kXPerThread; ++j) {
+      const int e = tid + j * kThreads;
       const int row = e / (KC / 8), col = (e % (KC / 8)) * 8;
       xr[slot][j] = load_h8(a.X + clamp_hi(row, a.M - 1) * K + k0 + col);
     }
   };
-  // INT4: X is stored already permuted to the codes' interleaved order
-  // (once per workgroup rather than once per wave and use)
+  // X is stored already permuted to the codes' interleaved order (once per
+  // workgroup rather than once per wave and use)
   const auto store_x = [&](int b, int slot) {
 #pragma unroll
-    for (int j = 0; j < C::kXPerThread; ++j) {
-      const int e = tid + j * C::kThreads;
-      if (e < C::kXH8) {
-        const int row = e / (KC / 8), col = (e % (KC / 8)) * 8;
-        *reinterpret_cast<h8*>(&Xs[b][row * C::kXLd + col]) =
-            W4 ? interleave_h8(xr[slot][j]) : xr[slot][j];
-      }
+    for (int j = 0; j < kXPerThread; ++j) {
+      const int e = tid + j * kThreads;
+      const int row = e / (KC / 8), col = (e % (KC / 8)) * 8;
+      *reinterpret_cast<h8*>(&Xs[b][row * kXLd + col]) = interleave_h8(xr[slot][j]);
     }
   };
-  f4 acc[NF][MF];
+  f4 acc[MF];
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
-#pragma unroll
-    for (int mf = 0; mf < MF; ++mf) acc[f][mf] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int mf = 0; mf < MF; ++mf) acc[mf] = f4{0.f, 0.f, 0.f, 0.f};
   const auto compute = [&](const WChunk& F, int b) {
 #pragma unroll
     for (int t = 0; t < KC / 128; ++t) {
-      h2 s2[NF], m2[NF];
-      if constexpr (W4) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) scale_min_pairs(F.sm[f][t], s2[f], m2[f]);
-      }
+      h2 s2, m2;
+      scale_min_pairs(F.sm[t], s2, m2);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int kl = 128 * t + (W4 ? 32 * g + 8 * i : 32 * i + 8 * g);
-        h8 xv[MF];
+        const int kl = 128 * t + 32 * g + 8 * i;
+        const h8 wv = dequant8_interleaved(F.w[t][i], s2, m2);
 #pragma unroll
         for (int mf = 0; mf < MF; ++mf)
-          xv[mf] = *reinterpret_cast<const h8*>(&Xs[b][(16 * mf + r) * C::kXLd + kl]);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          const h8 wv = W4 ? dequant8_interleaved(F.w[f][t][i], s2[f], m2[f])
-                           : __builtin_bit_cast(h8, F.w[f][4 * t + i]);
-#pragma unroll
-          for (int mf = 0; mf < MF; ++mf) acc[f][mf] = mfma16(wv, xv[mf], acc[f][mf]);
-        }
+          acc[mf] = mfma16(
+              wv, *reinterpret_cast<const h8*>(&Xs[b][(16 * mf + r) * kXLd + kl]), acc[mf]);
       }
     }
   };
@@ -428,20 +301,18 @@ __global__ __launch_bounds__(KW * 64) void gemm_stream(GemmArgs a, float* part, 
     }
   }
 
-  // acc[f][mf] element j: W row nw0 + 16 f + 4 g + j, X row 16 mf + r
+  // acc[mf] element j: W row nw0 + 4 g + j, X row 16 mf + r
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
+  for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
-    for (int mf = 0; mf < MF; ++mf)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t m = 16 * mf + r, n = nw0 + 16 * f + 4 * g + j;
-        if (gridDim.y == 1) {
-          epilogue<EPI>(a, m, n, acc[f][mf][j]);
-        } else if (m < a.M && n < a.N) {
-          part[((int64_t)blockIdx.y * a.M + m) * a.N + n] = acc[f][mf][j];
-        }
+    for (int j = 0; j < 4; ++j) {
+      const int64_t m = 16 * mf + r, n = nw0 + 4 * g + j;
+      if (gridDim.y == 1) {
+        epilogue<EPI>(a, m, n, acc[mf][j]);
+      } else if (m < a.M && n < a.N) {
+        part[((int64_t)blockIdx.y * a.M + m) * a.N + n] = acc[mf][j];
       }
+    }
 }
 
 // out = sum over z = 0 .. S-1 (in that order, from 0) of part[z], then the
@@ -488,18 +359,27 @@ static void launch_combine_v(const GemmArgs& a, const float* ws, int S, hipStrea
 }
 
 template <int EPI>
-static void launch_combine(const GemmArgs& a, const float* ws, int S, hipStream_t st) {
+static void launch_combine_epi(const GemmArgs& a, const float* ws, int S, hipStream_t st) {
   if (a.N % 4 == 0 && reinterpret_cast<uintptr_t>(ws) % 16 == 0)
     launch_combine_v<EPI, 4>(a, ws, S, st);
   else
     launch_combine_v<EPI, 1>(a, ws, S, st);
 }
 
+void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStream_t st) {
+  switch (epi) {
+    case EPI_F16: return launch_combine_epi<EPI_F16>(a, ws, S, st);
+    case EPI_RELU_F16: return launch_combine_epi<EPI_RELU_F16>(a, ws, S, st);
+    case EPI_ADD_F32: return launch_combine_epi<EPI_ADD_F32>(a, ws, S, st);
+    case EPI_F32: return launch_combine_epi<EPI_F32>(a, ws, S, st);
+    default: return launch_combine_epi<EPI_QKV>(a, ws, S, st);
+  }
+}
+
 // ---------------------------------------------------------------------------
-// tiled GEMM (prefill)
+// tiled GEMM (operands off 16-byte alignment)
 constexpr int kTBM = 128, kTBN = 128, kTBK = 64, kTPad = 8;
 constexpr int kTThreads = 256;  // 2 x 2 waves of 64 x 64
-constexpr int kXcds = 8;        // accelerator complex dies of an MI355X, each with its own L2
 constexpr int kTGroupM = 4;
 
 template <bool W4, int EPI, bool PK>
@@ -642,18 +522,11 @@ __global__ __launch_bounds__(kTThreads) void gemm_tiled(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// big-tile GEMMs (prefill with at least kBigMinTiles 256 x 256 tiles, enough
-// to fill the chip twice over): each W element read into LDS feeds 256 rows
-// of X instead of 128, and each LDS operand read feeds more MFMAs.  Same
-// tile order as gemm_tiled; the same MFMA per 32-wide k block in the same k
-// order, so for a given K every kernel gives the same bits.
+// big-tile GEMMs (prefill): each W element read into LDS feeds 256 rows of X
+// instead of 128, and each LDS operand read feeds more MFMAs.  Same tile
+// order as gemm_tiled; the same MFMA per 32-wide k block in the same k order,
+// so over one K range every kernel with one K group gives the same bits.
 // ---------------------------------------------------------------------------
-constexpr int64_t kBigMinTiles = 512;
-
-__host__ __device__ constexpr int64_t big_tiles(int64_t M, int64_t N) {
-  return ((M + 255) / 256) * ((N + 255) / 256);
-}
-
 constexpr int kBM = 256, kBN = 256;
 
 // fp16 W (fragment order, or row-major: PK): 8 waves (two per SIMD) of 128 x 64 (8 x 4
@@ -678,7 +551,8 @@ constexpr int kFThreads = 512;
 constexpr int kFStages = 4;              // LDS stages of the INT4 kernel's ring
 
 template <int EPI, bool PK>
-__global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a) {
+__global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a, float* part,
+                                                          int64_t kper) {
   constexpr int FM = 8, FN = 4;  // fragments per wave
   constexpr int BPW = 2;         // W row blocks each wave moves per stage
   constexpr int PER_STAGE = 2 * BPW;
@@ -701,7 +575,8 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a) {
   const int64_t m0 = (first_m + in_group % gm) * kBM;
   const int64_t n0 = (in_group / gm) * kBN;
   const int64_t K = a.K;
-  const int KT = (int)(K / 32);
+  const int64_t kbeg = (int64_t)blockIdx.y * kper;
+  const int KT = (int)(kper / 32);
   const int KS = KT / 2;         // 64-wide X stages
 
   const int r = lane & 15, g = lane >> 4;
@@ -717,7 +592,7 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a) {
       const int c = (lane & 7) ^ ((row >> 1) & 7);
       int64_t m = m0 + 16 * (2 * wave + bb) + row;
       m = m < a.M ? m : a.M - 1;
-      xsrc[bb][q] = a.X + m * K + 8 * c;
+      xsrc[bb][q] = a.X + m * K + kbeg + 8 * c;
     }
   const uint16_t* bsrc[BPW];
 #pragma unroll
@@ -725,11 +600,11 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a) {
     if constexpr (PK) {
       int64_t nb = (n0 >> 4) + BPW * wave + i;
       nb = nb < (a.N >> 4) ? nb : (a.N >> 4) - 1;
-      bsrc[i] = a.W + nb * (K >> 5) * 512 + lane * 8;
+      bsrc[i] = a.W + (nb * (K >> 5) + (kbeg >> 5)) * 512 + lane * 8;
     } else {
       int64_t n = n0 + 16 * (BPW * wave + i) + r;
       n = n < a.N ? n : a.N - 1;
-      bsrc[i] = a.W + n * K + 8 * g;
+      bsrc[i] = a.W + n * K + kbeg + 8 * g;
     }
   }
   constexpr int kBStep = PK ? 512 : 32;
@@ -814,6 +689,21 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a) {
   mma(fa1, fb1);
 
   // acc[i][j] element e: row m0 + 128 wm + 16 i + 4 g + e, col n0 + 64 wn + 16 j + r
+  if (gridDim.y > 1) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t m = m0 + wm * 128 + i * 16 + 4 * g + e;
+        float* p = part + ((int64_t)blockIdx.y * a.M + m) * a.N;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const int64_t n = n0 + wn * 64 + j * 16 + r;
+          if (m < a.M && n < a.N) p[n] = acc[i][j][e];
+        }
+      }
+    return;
+  }
   float bias[FN];
 #pragma unroll
   for (int j = 0; j < FN; ++j) bias[j] = epilogue_bias(a, n0 + wn * 64 + j * 16 + r);
@@ -978,101 +868,145 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_w4(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// skinny configurations by M: (waves, steps in flight per wave)
+// The kernel of a shape, from (M, N, K) and the weight format (and for two
+// cases the layout and alignment).  Times are us of one launch with its
+// merge over rotating weights (fragment order unless stated).
 // ---------------------------------------------------------------------------
-template <int MF> struct SkinnyCfg;
-template <> struct SkinnyCfg<1> { static constexpr int KW = 8, UNR = 2; };
+constexpr int64_t kSkinnyMaxM = 16, kDecodeMaxM = 128;
+constexpr int kMaxSplits = 8;
+// About one workgroup per CU measured best: a slab workgroup takes most of a
+// CU's LDS, so more of them only queue.
+constexpr int64_t kMaxWGs = 256;
 
-template <int NF, bool W4, int EPI, bool PK>
-static void launch_skinny(const GemmArgs& a, hipStream_t st) {
-  using C = SkinnyCfg<1>;
-  const dim3 grid((unsigned)((a.N + 16 * NF - 1) / (16 * NF)));
-  launch((gemm_skinny<NF, 1, C::KW, C::UNR, W4, EPI, PK>), grid, dim3(C::KW * 64), 0, st, a);
-}
-
-// streaming configurations by (W format, 16-row blocks of X): rows per
-// wave (16 NF), waves, chunks in flight, chunk length; and a fallback with
-// 128-k chunks for K that the chunk length does not divide
-template <bool W4, int MF> struct StreamSel;
-template <> struct StreamSel<false, 2> { static constexpr int NF = 1, KW = 8, PD = 2, KC = 128; };
-template <> struct StreamSel<false, 4> { static constexpr int NF = 1, KW = 8, PD = 2, KC = 128; };
-template <> struct StreamSel<false, 8> { static constexpr int NF = 1, KW = 8, PD = 2, KC = 128; };
-template <> struct StreamSel<true, 2> { static constexpr int NF = 1, KW = 8, PD = 2, KC = 256; };
-template <> struct StreamSel<true, 4> { static constexpr int NF = 2, KW = 8, PD = 4, KC = 256; };
-template <> struct StreamSel<true, 8> { static constexpr int NF = 2, KW = 8, PD = 4, KC = 128; };
-template <bool W4, int MF> struct StreamFallback {
-  static constexpr int NF = StreamSel<W4, MF>::NF, KW = StreamSel<W4, MF>::KW;
-  static constexpr int PD = StreamSel<W4, MF>::KC == 128 ? StreamSel<W4, MF>::PD : 2 * StreamSel<W4, MF>::PD;
-  static constexpr int KC = 128;
+enum GemmKernel { kSkinny, kSlab, kStreamW4, kBig, kTiled };
+struct GemmPlan {
+  GemmKernel kernel;
+  int slab = 0;    // row of the slab tables
+  int splits = 1;  // K ranges
 };
 
-constexpr int kStreamMaxM = 128;
-constexpr int kStreamMaxSplits = 8;
-constexpr int64_t kStreamMaxWGs = 256;  // about one workgroup per CU measured best
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-static int stream_mf(int64_t M) { return M <= 32 ? 2 : (M <= 64 ? 4 : 8); }
-
-// K split: the largest power of two (up to the cap) that keeps the grid
-// within kStreamMaxWGs workgroups and the split a multiple of the chunk
-static int stream_splits(int64_t N, int64_t K, int rows_per_wg, int kc) {
-  const int64_t blocks = (N + rows_per_wg - 1) / rows_per_wg;
+// K ranges: the largest power of two up to the cap that keeps the grid within
+// kMaxWGs workgroups and every range at least kper_min long
+static int split_k(int64_t wgs, int64_t K, int64_t kper_min) {
   int S = 1;
-  while (S < kStreamMaxSplits && blocks * 2 * S <= kStreamMaxWGs && K % (2ll * S * kc) == 0)
+  while (S < kMaxSplits && wgs * 2 * S <= kMaxWGs && K % (2ll * S * 128) == 0 &&
+         K / (2 * S) >= kper_min)
     S *= 2;
   return S;
 }
 
-// fp16 shapes whose unsplit 8-wave grid would leave many CUs idle (under
-// kStreamMinWGs workgroups) take 6 waves per workgroup instead: more
-// workgroups, each output summed by one wave in the same order as before
-constexpr int kStreamNarrowKW = 6;
-constexpr int64_t kStreamMinWGs = 192;
+// rows of the slab tables (gemm_common.h) by what they are for
+enum { kF16M16n16 = 0, kF16M16n32, kF16M32n32, kF16M32n96, kF16M32n128, kF16M64n64, kF16M64n96,
+       kF16M64n128, kF16M128n64, kF16M128n128 };
+enum { kW4M16n32 = 0, kW4M32n64, kW4M32n128, kW4M64n64, kW4M64n128, kW4M128n64, kW4M128n128,
+       kW4M128n256, kW4M128n256k1 };
 
-struct StreamPlan {
-  bool fallback, narrow;
-  int rows_per_wg, kc, splits;
-};
+// M <= 16.  The skinny kernel has no LDS staging and no barrier, and its 16
+// or 64 rows per workgroup fill the chip at many N; what it lacks is the
+// balance at N of 5120 to 8192, where 320 to 512 workgroups of 16 rows leave
+// a second round half empty and X is read by each: there 32-row slab
+// workgroups (at most 256) take over, K split over their waves.  M = 16: fp16
+// 7168 x 28672 82.9 -> 61.8, 6144 x 4096 14.4 -> 11.1, INT4 63.2 -> 35.7 and
+// 11.4 -> 8.5; at M <= 8 the two are equal (17.6 against 17.9) but for fp16
+// and long K (M = 1, 5120 x 20480: 41.0 -> 34.6).  Below, 16-row slab
+// workgroups for fp16 (M = 16, 4096 x 14336: 23.3 -> 22.0; INT4 fragments
+// come in pairs, 32 rows, which would leave half the CUs idle).  With fp16 W
+// both kernels give the same bits; with INT4 W an EPI_F16 output stays with
+// the skinny kernel: EPI_SWIGLU, which only that kernel has, gives the values
+// of EPI_F16 and the SwiGLU kernel bit for bit.
+static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi) {
+  if (w4 && epi == EPI_F16) return {kSkinny};
+  const bool rows16 = M > 8, longk = !w4 && K >= 16384;
+  if (N >= 5120 && N <= 8192 && (rows16 || longk))
+    return {kSlab, w4 ? kW4M16n32 : kF16M16n32};
+  if (N < 5120 && rows16 && !w4) return {kSlab, kF16M16n16};
+  return {kSkinny};
+}
 
-template <bool W4, int MF>
-static StreamPlan stream_plan_mf(int64_t N, int64_t K) {
-  using P = StreamSel<W4, MF>;
-  using B = StreamFallback<W4, MF>;
-  StreamPlan pl;
-  pl.fallback = K % P::KC != 0;
-  pl.narrow = false;
-  pl.rows_per_wg = pl.fallback ? 16 * B::NF * B::KW : 16 * P::NF * P::KW;
-  pl.kc = pl.fallback ? B::KC : P::KC;
-  pl.splits = stream_splits(N, K, pl.rows_per_wg, pl.kc);
-  if (!W4 && !pl.fallback && pl.splits == 1) {
-    const int rows6 = 16 * P::NF * kStreamNarrowKW;
-    if ((N + pl.rows_per_wg - 1) / pl.rows_per_wg < kStreamMinWGs &&
-        (N + rows6 - 1) / rows6 <= kStreamMaxWGs) {
-      pl.narrow = true;
-      pl.rows_per_wg = rows6;
+// 16 < M <= 128: the slab kernel with 64 columns per workgroup while that
+// fills the chip (N up to 16384), else 128.  Long K goes to the wide
+// workgroups too: each reads all of X, and K ranges give the workgroups
+// (fp16 M = 64, 7168 x 28672: 81.5 with 64 columns and 2 ranges, 70.6 with
+// 128 and 4; at 8192 x 8192 29.4 against 32.4).  fp16 grids of 128-column
+// workgroups that leave a quarter of the CUs idle (N of 16384 to 24576; at
+// M <= 32 from 8192) take 96 columns (M = 64, 21504 x 7168: 62.5 -> 51.9); at
+// M <= 32 and N <= 8192 32 columns and no split measured best (8192 x 8192:
+// 29.3 -> 24.0).  Splitting K pays only for its second launch (about 2.5 us)
+// when a range is long enough: not below K = 1536.
+static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4) {
+  const int mf = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
+  GemmPlan p{kSlab};
+  int cols;
+  if (w4) {
+    const bool narrow = N <= 16384 && K < (mf == 8 ? 8193 : (mf == 4 ? 16384 : 14336));
+    p.slab = (mf == 2 ? kW4M32n64 : (mf == 4 ? kW4M64n64 : kW4M128n64)) + (narrow ? 0 : 1);
+    cols = narrow ? 64 : 128;
+  } else if (mf == 2) {
+    if (N <= 8192 && K <= 8192) {
+      p.slab = kF16M32n32;
+      cols = 32;
+    } else if (N > 8192 && N <= 24576) {
+      p.slab = kF16M32n96;
+      cols = 96;
+    } else {
+      p.slab = kF16M32n128;
+      cols = 128;
     }
+  } else if (mf == 4 && N > 16384 && N <= 24576) {
+    p.slab = kF16M64n96;
+    cols = 96;
+  } else {
+    const bool narrow = N <= 16384 && K < (mf == 8 ? 6145 : 16384);
+    p.slab = mf == 4 ? (narrow ? kF16M64n64 : kF16M64n128) : (narrow ? kF16M128n64 : kF16M128n128);
+    cols = narrow ? 64 : 128;
   }
-  return pl;
+  if (K >= 1536) p.splits = split_k(ceil_div(N, cols), K, 256);
+  return p;
 }
 
-static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K, bool w4) {
-  switch (stream_mf(M)) {
-    case 2: return w4 ? stream_plan_mf<true, 2>(N, K) : stream_plan_mf<false, 2>(N, K);
-    case 4: return w4 ? stream_plan_mf<true, 4>(N, K) : stream_plan_mf<false, 4>(N, K);
-    default: return w4 ? stream_plan_mf<true, 8>(N, K) : stream_plan_mf<false, 8>(N, K);
+// M > 128 (prefill): 256 x 256 tiles while they fill the chip, else smaller
+// tiles and K ranges.  INT4: the 128-row slab kernels below 192 big tiles
+// (us at M = 512: 4096 x 14336 301 with 128 x 128 tiles -> 72, 28672 x 4096,
+// 224 big tiles, 227 -> 129; M = 2048, 4096 x 4096, 128 big tiles: 104 big,
+// 70 slab); 128 columns while one K range gives at most kMaxWGs workgroups,
+// else 256.  Their two K groups sum in another order than the big tiles; K
+// under 512 (four chunks a group) stays with one group.  fp16: big tiles with
+// K ranges (M = 512, 4096 x 14336: 202 -> 71; 28672 x 4096 202 -> 104), and
+// 128 x 128 slab tiles where even 8 ranges give few workgroups (M = 200,
+// 768 x 3072: 46 -> 15).  Outputs of fewer than 512 columns are no layer's
+// and stay unsplit.
+static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4) {
+  const int64_t big = ceil_div(M, 256) * ceil_div(N, 256), mt = ceil_div(M, 128);
+  const int64_t kper = N < 512 ? K : 512;
+  if (w4) {
+    if (big >= 192) return {kBig};
+    if (K < 512) return {kSlab, kW4M128n256k1};
+    const int64_t t128 = mt * ceil_div(N, 128);
+    if (t128 <= kMaxWGs && K < 8192) return {kSlab, kW4M128n128, split_k(t128, K, kper)};
+    return {kSlab, kW4M128n256, split_k(mt * ceil_div(N, 256), K, kper)};
   }
+  const int S = split_k(big, K, kper);
+  if (big * S <= 64) return {kSlab, kF16M128n128, split_k(mt * ceil_div(N, 128), K, kper)};
+  return {kBig, 0, S};
 }
 
-static bool uses_stream(int64_t M) { return M > 16 && M <= kStreamMaxM; }
+static GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool w4, int epi) {
+  if (M <= kSkinnyMaxM) return plan_m16(M, N, K, w4, epi);
+  return M <= kDecodeMaxM ? plan_decode(M, N, K, w4) : plan_prefill(M, N, K, w4);
+}
 
 int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4) {
-  if (!uses_stream(M) || N <= 0 || K <= 0 || K % 128 != 0) return 0;
-  const StreamPlan pl = stream_plan(M, N, K, w4);
-  return pl.splits > 1 ? (int64_t)pl.splits * M * N * 4 : 0;
+  if (M <= kSkinnyMaxM || N <= 0 || K <= 0 || K % 128 != 0) return 0;
+  const GemmPlan p = gemm_plan(M, N, K, w4, EPI_F32);  // (no epilogue changes a split)
+  return p.splits > 1 ? (int64_t)p.splits * M * N * 4 : 0;
 }
 
+// the decode sizes only: a prefill GEMM takes as many K ranges as fit in it
 int64_t gemm_workspace_bytes_upto(int64_t M_max, int64_t N, int64_t K, bool w4) {
   int64_t best = 0;
-  for (int64_t M : {(int64_t)32, (int64_t)64, (int64_t)kStreamMaxM}) {
+  for (int64_t M : {(int64_t)32, (int64_t)64, kDecodeMaxM}) {
     const int64_t m = M < M_max ? M : M_max;
     const int64_t b = gemm_workspace_bytes(m, N, K, w4);
     best = b > best ? b : best;
@@ -1080,31 +1014,20 @@ int64_t gemm_workspace_bytes_upto(int64_t M_max, int64_t N, int64_t K, bool w4) 
   return best;
 }
 
-template <int NF, int MF, int KW, int PD, bool W4, int KC, int EPI, bool PK>
-static void launch_stream_cfg(const GemmArgs& a, int S, float* ws, hipStream_t st) {
-  constexpr int rows = 16 * NF * KW;
-  const dim3 grid((unsigned)((a.N + rows - 1) / rows), (unsigned)S);
-  launch((gemm_stream<NF, MF, KW, PD, W4, KC, EPI, PK>), grid, dim3(KW * 64), 0, st, a, ws,
-         a.K / S);
-  if (S > 1) launch_combine<EPI>(a, ws, S, st);
+template <int NF, bool W4, int EPI, bool PK>
+static void launch_skinny(const GemmArgs& a, hipStream_t st) {
+  constexpr int KW = 8, UNR = 2;  // waves, steps in flight per wave
+  const dim3 grid((unsigned)((a.N + 16 * NF - 1) / (16 * NF)));
+  launch((gemm_skinny<NF, 1, KW, UNR, W4, EPI, PK>), grid, dim3(KW * 64), 0, st, a);
 }
 
-template <bool W4, int MF, int EPI, bool PK>
-static void launch_stream_mf(const GemmArgs& a, const StreamPlan& pl, int S, float* ws,
-                             hipStream_t st) {
-  if (pl.fallback) {
-    using B = StreamFallback<W4, MF>;
-    launch_stream_cfg<B::NF, MF, B::KW, B::PD, W4, B::KC, EPI, PK>(a, S, ws, st);
-  } else {
-    using P = StreamSel<W4, MF>;
-    if constexpr (!W4) {
-      if (pl.narrow) {
-        launch_stream_cfg<P::NF, MF, kStreamNarrowKW, P::PD, W4, P::KC, EPI, PK>(a, S, ws, st);
-        return;
-      }
-    }
-    launch_stream_cfg<P::NF, MF, P::KW, P::PD, W4, P::KC, EPI, PK>(a, S, ws, st);
-  }
+template <int EPI>
+static void launch_stream_w4(const GemmArgs& a, int S, float* ws, hipStream_t st) {
+  const dim3 grid((unsigned)ceil_div(a.N, kStreamRows), (unsigned)S), block(kStreamKW * 64);
+  if (a.K % (256 * S) == 0)
+    launch((gemm_stream_w4<2, 256, EPI>), grid, block, 0, st, a, ws, a.K / S);
+  else
+    launch((gemm_stream_w4<4, 128, EPI>), grid, block, 0, st, a, ws, a.K / S);
 }
 
 template <bool W4, int EPI, bool PK>
@@ -1112,7 +1035,7 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
   if constexpr (EPI == EPI_SWIGLU) {
     (void)ws;
     (void)ws_bytes;
-    if (a.M > 16) {
+    if (a.M > kSkinnyMaxM) {
       set_error("gemm: the SwiGLU epilogue needs M <= 16 (M=%lld)", (long long)a.M);
       return PIPO_ERR_UNSUPPORTED;
     }
@@ -1120,36 +1043,51 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
     PIPO_HIP_TRY(hipGetLastError());
     return PIPO_OK;
   } else {
-    if (a.M <= 16) {
-      // 64 W rows per workgroup (less X traffic per W byte) once that still
-      // gives enough workgroups to fill the chip, else 16
-      if (a.N >= 64 * 192)
-        launch_skinny<4, W4, EPI, PK>(a, st);
-      else
-        launch_skinny<1, W4, EPI, PK>(a, st);
-    } else if (a.M <= kStreamMaxM) {
-      const StreamPlan pl = stream_plan(a.M, a.N, a.K, W4);
-      // without room for the partial sums the K split is dropped
-      const int S = (pl.splits > 1 && ws != nullptr && a.M * a.N < ((int64_t)1 << 31) &&
-                     ws_bytes >= (int64_t)pl.splits * a.M * a.N * 4) ? pl.splits : 1;
-      switch (stream_mf(a.M)) {
-        case 2: launch_stream_mf<W4, 2, EPI, PK>(a, pl, S, ws, st); break;
-        case 4: launch_stream_mf<W4, 4, EPI, PK>(a, pl, S, ws, st); break;
-        default: launch_stream_mf<W4, 8, EPI, PK>(a, pl, S, ws, st); break;
+    GemmPlan p = gemm_plan(a.M, a.N, a.K, W4, EPI);
+    // as many of the planned K ranges as the workspace has room for
+    while (p.splits > 1 && (ws == nullptr || a.M * a.N >= ((int64_t)1 << 31) ||
+                            ws_bytes < (int64_t)p.splits * a.M * a.N * 4))
+      p.splits /= 2;
+    // row-major INT4 at M <= 32: see gemm_stream_w4 (same K ranges)
+    if (W4 && !PK && p.kernel == kSlab && p.slab == kW4M32n128) p.kernel = kStreamW4;
+    // loads straight into LDS take 16 bytes at a time: operands off that
+    // alignment go to the kernels that load through registers
+    const uintptr_t at = reinterpret_cast<uintptr_t>(a.X) |
+                         (W4 ? reinterpret_cast<uintptr_t>(a.Wq) : reinterpret_cast<uintptr_t>(a.W));
+    if (at % 16 != 0 || (W4 && reinterpret_cast<uintptr_t>(a.Wsm) % 4 != 0))
+      p = GemmPlan{a.M <= kSkinnyMaxM ? kSkinny : kTiled};
+    switch (p.kernel) {
+      case kSkinny:
+        // 64 W rows per workgroup (less X traffic per W byte) once that still
+        // gives enough workgroups to fill the chip, else 16
+        if (a.N >= 64 * 192)
+          launch_skinny<4, W4, EPI, PK>(a, st);
+        else
+          launch_skinny<1, W4, EPI, PK>(a, st);
+        break;
+      case kSlab:
+        (W4 ? launch_slab_w4 : launch_slab_f16)(a, EPI, p.slab, p.splits, ws, st);
+        break;
+      case kStreamW4:
+        if constexpr (W4 && !PK) launch_stream_w4<EPI>(a, p.splits, ws, st);
+        break;
+      case kBig: {
+        const int64_t per_xcd = ceil_div(ceil_div(a.M, kBM) * ceil_div(a.N, kBN), kXcds);
+        const dim3 grid((unsigned)(per_xcd * kXcds), (unsigned)p.splits);
+        if constexpr (W4)
+          launch((gemm_big_w4<EPI, PK>), grid, dim3(kFThreads), 0, st, a);
+        else
+          launch((gemm_big_f16<EPI, PK>), grid, dim3(kFThreads), 0, st, a, ws, a.K / p.splits);
+        break;
       }
-    } else if (big_tiles(a.M, a.N) >= kBigMinTiles) {
-      const int64_t per_xcd = (big_tiles(a.M, a.N) + kXcds - 1) / kXcds;
-      const dim3 grid((unsigned)(per_xcd * kXcds));
-      if constexpr (W4)
-        launch((gemm_big_w4<EPI, PK>), grid, dim3(kFThreads), 0, st, a);
-      else
-        launch((gemm_big_f16<EPI, PK>), grid, dim3(kFThreads), 0, st, a);
-    } else {
-      const int64_t total = ((a.N + kTBN - 1) / kTBN) * ((a.M + kTBM - 1) / kTBM);
-      const int64_t per_xcd = (total + kXcds - 1) / kXcds;
-      launch((gemm_tiled<W4, EPI, PK>), dim3((unsigned)(per_xcd * kXcds)), dim3(kTThreads), 0, st,
-             a);
+      case kTiled: {
+        const int64_t per_xcd = ceil_div(ceil_div(a.M, kTBM) * ceil_div(a.N, kTBN), kXcds);
+        launch((gemm_tiled<W4, EPI, PK>), dim3((unsigned)(per_xcd * kXcds)), dim3(kTThreads), 0, st,
+               a);
+        break;
+      }
     }
+    if (p.splits > 1) launch_combine(a, EPI, ws, p.splits, st);
     PIPO_HIP_TRY(hipGetLastError());
     return PIPO_OK;
   }

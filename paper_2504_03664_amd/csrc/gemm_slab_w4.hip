@@ -1,0 +1,16 @@
+// Slab GEMMs with INT4 W (gemm_slab.h), one kernel per row of the table in
+// gemm_common.h, epilogue and layout.
+#include "gemm_slab.h"
+
+namespace pipo {
+
+void launch_slab_w4(const GemmArgs& a, int epi, int idx, int S, float* ws, hipStream_t st) {
+  switch (idx) {
+#define PIPO_CASE(i, MF, NF, WN, KS, PD) \
+  case i: return launch_slab<MF, NF, WN, KS, PD, true>(a, epi, S, ws, st);
+    PIPO_SLAB_W4(PIPO_CASE)
+#undef PIPO_CASE
+  }
+}
+
+}  // namespace pipo

@@ -1,0 +1,72 @@
+"""GEMM shapes at the edges of the dispatch (gemm.hip, gemm_plan): every slab
+configuration with ragged rows, columns and chunk counts, K ranges with and
+without room for their partials, and operands off the 16-byte alignment that
+loads into LDS need.  Small integers, so every order of summation gives the
+oracle's product exactly."""
+import numpy as np
+import pytest
+
+from oracle import dequant_int4_g64
+from paper_2504_03664_amd import binding as B
+from paper_2504_03664_amd.binding import DeviceBuffer as DB
+from test_gpu_ops import run_gemm
+
+pytestmark = pytest.mark.gpu
+
+DECODE = [(9, 5136, 384), (16, 8192, 128), (13, 80, 640),           # M <= 16
+          (17, 80, 640), (32, 80, 2048), (31, 8208, 128), (20, 16400, 128), (32, 24592, 256),
+          (33, 80, 384), (64, 144, 2048), (50, 16400, 128), (64, 24592, 128),
+          (65, 80, 640), (128, 144, 2048), (100, 16400, 128), (127, 16400, 384)]
+PREFILL = [(129, 528, 2048), (130, 768, 3072), (200, 1040, 8192), (257, 4112, 1024),
+           (300, 16400, 128), (1030, 528, 1152)]
+
+
+def _case(M, N, K, w4):
+    rng = np.random.default_rng(M * 31 + N + K + w4)
+    X = rng.integers(-1, 2, (M, K)).astype(np.float64)
+    if not w4:
+        W = rng.integers(-2, 3, (N, K)).astype(np.float64)
+        return X, W, None, X @ W.T
+    codes = rng.integers(0, 16, (N, K))
+    q = (codes[:, 0::2] | (codes[:, 1::2] << 4)).astype(np.uint8)
+    sm = np.empty((N, K // 64, 2), np.float16)
+    sm[..., 0] = rng.choice([0.5, 1.0], (N, K // 64))
+    sm[..., 1] = rng.choice([-3.0, 0.0], (N, K // 64))
+    return X, None, (q, sm), X @ dequant_int4_g64(q, sm, np.float64).T
+
+
+@pytest.mark.parametrize("M,N,K", DECODE + PREFILL)
+@pytest.mark.parametrize("w4", [False, True])
+def test_gemm_plan_edges_exact(M, N, K, w4):
+    X, W, q, want = _case(M, N, K, w4)
+    rng = np.random.default_rng(N)
+    init = rng.integers(-100, 100, (M, N)).astype(np.float64)
+    bias = rng.integers(-8, 9, N).astype(np.float64)
+    for frag in (False, True):
+        for ws in (True, False):
+            print(f"gemm plan M={M} N={N} K={K} w4={w4} frag={frag} workspace={ws}", flush=True)
+            got = run_gemm(X, W, bias, B.PIPO_EPI_ADD_F32, init, w4=q, workspace=ws, frag=frag)
+            assert np.array_equal(got.astype(np.float64), init + want + bias)
+    got = run_gemm(X, W, bias, B.PIPO_EPI_RELU_F16, w4=q, frag=True)
+    assert np.array_equal(got, np.maximum(want + bias, 0).astype(np.float16))
+
+
+@pytest.mark.parametrize("M", [4, 16, 40, 128, 300])
+@pytest.mark.parametrize("w4", [False, True])
+def test_gemm_unaligned_operands_exact(M, w4):
+    """X two bytes, or INT4 codes four bytes, past a 16-byte boundary."""
+    N, K = 5136, 256
+    X, W, q, want = _case(M, N, K, w4)
+    print(f"gemm unaligned M={M} w4={w4}", flush=True)
+    dO = DB(M * N * 4)
+    if w4:
+        dX, dsm = DB.from_array(X.astype(np.float16)), DB.from_array(q[1])
+        dW = DB.from_array(np.concatenate([np.zeros(4, np.uint8), q[0].reshape(-1)]))
+        B.pipo_op_gemm_w4(dX.ptr, dW.ptr + 4, dsm.ptr, None, dO.ptr, M, N, K, B.PIPO_EPI_F32)
+    else:
+        dX = DB.from_array(np.concatenate([np.zeros(1, np.float16),
+                                           X.astype(np.float16).reshape(-1)]))
+        dW = DB.from_array(W.astype(np.float16))
+        B.pipo_op_gemm_f16(dX.ptr + 2, dW.ptr, None, dO.ptr, M, N, K, B.PIPO_EPI_F32)
+    B.pipo_dev_synchronize()
+    assert np.array_equal(dO.to_array(np.float32, (M, N)).astype(np.float64), want)
