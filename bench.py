@@ -32,7 +32,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "decode tokens/s at 1 GPU; % of H2D-link roofline; GPU-busy %"
-KERNEL_SOURCES = ("gemm.hip", "gemm_slab.h", "gemm_common.h", "attention.hip", "device.h")
+KERNEL_SOURCES = ("gemm.hip", "gemm_slab.h", "gemm_common.h", "attention.hip", "attention_gqa.hip",
+                  "attention_common.h", "device.h")
 HBM_PEAK_GBPS = 8000.0
 MFMA_F16_PEAK_TFLOPS = 2500.0
 
@@ -460,13 +461,15 @@ def main():
         elif fam_key == "attention":
             kv4 = "true" if wl.kv_fmt == "int4" else "false"
             G = shape.n_heads // hkv
-            hp = 1 if G > 1 else (4 if hkv % 4 == 0 else (2 if hkv % 2 == 0 else 1))
+            hp = 4 if hkv % 4 == 0 else (2 if hkv % 2 == 0 else 1)
             # fp16 rows: the library narrows workgroups to fewer heads while
             # that leaves fewer than 1536 of them
             while kv4 == "false" and hp > 1 and wl.batch * (hkv // hp) < 1536:
                 hp //= 2
-            symbols = ([f"attn_decode_kv4_k<{dh}, {hp}>"] if kv4 == "true" and G == 1
-                       else [f"attn_decode_k<{dh}, {G}, {hp}, {kv4}>"])
+            # grouped: eight waves while the (unsplit) grid fits the CUs
+            symbols = ([f"attn_decode_gqa_k<{dh}, {8 if wl.batch * hkv <= 256 else 4}, {kv4}, true>"]
+                       if G > 1 else [f"attn_decode_kv4_k<{dh}, {hp}>"] if kv4 == "true"
+                       else [f"attn_decode_k<{dh}, {hp}>"])
             # with key splits the launch also runs the merge kernel (one
             # dispatch per attention launch), whose bytes count too
             symbols_opt = [f"attn_decode_combine<{dh}>"]

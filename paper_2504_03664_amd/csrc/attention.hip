@@ -4,7 +4,8 @@
 // key/value head h / (H / Hkv).  This is the layout the copy engine streams when the cache lives
 // in host memory: a layer's prefix 0..t-1 is one contiguous range.
 //
-//   attn_decode:  one new query per (sequence, head) against keys 0..t.
+//   attn_decode:  one new query per (sequence, head) against keys 0..t
+//                 (with grouped-query attention: attention_gqa.hip).
 //   attn_prefill: P queries per (sequence, head), causal, flash-style with
 //                 v_mfma_f32_16x16x32_f16 for Q K^T and P V.
 // Softmax is max-subtracted in fp32; every reduction has a fixed order.
@@ -12,21 +13,9 @@
 #include <cfloat>
 #include <mutex>
 
-#include "common.h"
-#include "device.h"
+#include "attention_common.h"
 
 namespace pipo {
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
-}
 
 // Sum over aligned groups of N <= 16 lanes with DPP moves inside a row of 16
 // lanes (swap neighbours, swap pairs, mirror within 8, mirror within 16):
@@ -47,23 +36,19 @@ __device__ __forceinline__ float group_sum(float v) {
 }
 
 // ---------------------------------------------------------------------------
-// decode: grid (key/value head groups, b, splits), 256 threads.  A workgroup
-// serves HP adjacent key/value heads of one sequence and the G = H / Hkv
-// query heads that read each of them (HP > 1 only without grouping, G = 1),
-// so each cached row is read from HBM once per step and a key's HP heads
-// are one contiguous HP * D * 2-byte read.  Split z of a (sequence, head
-// group) covers keys [z * chunk, min(T, (z + 1) * chunk)).  A key's head is
-// handled by D/8 lanes (8 dims each; fp16 rows are read with non-temporal
-// loads, as every row is read once); every lane group keeps, per query
-// head, its own online softmax state (running max m, sum l, 8 accumulators)
-// over the keys it visits, two keys at a time so that K and V of both are
-// in flight together (the second one's index is clamped, so the loads are
-// unconditional).  Groups are merged by a butterfly inside the wave, waves
-// in order through LDS.  With one split the result is final; otherwise (m,
-// l, acc[D]) of each query head goes to `part` and attn_decode_combine
-// merges the splits in split order.  With KV4 the cache rows are INT4
-// (dkv/2 code bytes, then dkv/64 fp16 (scale, min) pairs): a lane reads its
-// 8 codes and its group's pair and expands them to fp16.
+// decode without grouping: grid (head groups, b, splits), 256 threads.  A
+// workgroup serves HP adjacent heads of one sequence, so each cached row is
+// read from HBM once per step and a key's HP heads are one contiguous HP * D
+// * 2-byte read.  Split z of a (sequence, head group) covers keys
+// [z * chunk, min(T, (z + 1) * chunk)).  A key's head is handled by D/8 lanes
+// (8 dims each; fp16 rows are read with non-temporal loads, as every row is
+// read once); every lane group keeps its own online softmax state (running
+// max m, sum l, 8 accumulators) over the keys it visits, two keys at a time
+// so that K and V of both are in flight together (the second one's index is
+// clamped, so the loads are unconditional).  Groups are merged by a butterfly
+// inside the wave, waves in order through LDS.  With one split the result is
+// final; otherwise (m, l, acc[D]) of each head goes to `part` and
+// attn_decode_combine merges the splits in split order.
 __device__ __forceinline__ void online_merge(float& m, float& l, float (&acc)[8], float m2,
                                              float l2, const float (&acc2)[8]) {
   const float M = fmaxf(m, m2);
@@ -75,112 +60,52 @@ __device__ __forceinline__ void online_merge(float& m, float& l, float (&acc)[8]
   m = M;
 }
 
-template <int D, int G, int HP, bool KV4>
+template <int D, int HP>
 __global__ __launch_bounds__(256) void attn_decode_k(const uint16_t* __restrict__ q,
-                                                     const void* __restrict__ kc,
-                                                     const void* __restrict__ vc,
+                                                     const uint16_t* __restrict__ kc,
+                                                     const uint16_t* __restrict__ vc,
                                                      uint16_t* __restrict__ o,
-                                                     float* __restrict__ part, int b, int Hkv,
+                                                     float* __restrict__ part, int b, int H,
                                                      int t, int chunk) {
-  static_assert(G == 1 || HP == 1, "several heads per workgroup only without grouping");
-  constexpr float kLog2e = 1.4426950408889634f;
   constexpr int LPP = D / 8;      // lanes per head of a key
   constexpr int LPK = HP * LPP;   // lanes per key
   constexpr int PPW = 64 / LPK;   // keys per wave per pass
-  constexpr int NQ = HP * G;      // query heads of the workgroup
-  __shared__ float wm[4][NQ], wl[4][NQ];
-  __shared__ float wacc[4][NQ * D];
+  __shared__ float wm[4][HP], wl[4][HP];
+  __shared__ float wacc[4][HP * D];
   const int kb = blockIdx.x, bi = blockIdx.y, sp = blockIdx.z, S = gridDim.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane / LPK, cl = lane % LPK, hl = cl / LPP, cd = (cl % LPP) * 8;
-  const int H = Hkv * G;
-  const int64_t d = (int64_t)H * D, dkv = (int64_t)Hkv * D;
+  const int64_t d = (int64_t)H * D;
   const int T = t + 1;
   const int p0 = sp * chunk, p1 = min(T, p0 + chunk);
-  const int kh = kb * HP + hl;                    // this lane's key/value head
-  const int64_t kcol = (int64_t)kh * D + cd;
+  const int64_t col = (int64_t)(kb * HP + hl) * D + cd;
 
-  float qf[G][8];
+  float qf[8];
+  const h8 qv = load_h8(q + (int64_t)bi * d + col);
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const h8 qv = load_h8(q + (int64_t)bi * d + (int64_t)(kh * G + g) * D + cd);
+  for (int i = 0; i < 8; ++i) qf[i] = (float)qv[i];
+  float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) qf[g][i] = (float)qv[i];
-  }
-  float m[G], l[G], acc[G][8];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY;
-    l[g] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[g][i] = 0.f;
-  }
+  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
 
-  // fp16: byte offset of this lane's 8 values in row `bi` of position 0;
-  // INT4: byte offsets of its 4 code bytes and of its group's (scale, min)
-  const int64_t row_bytes = KV4 ? dkv / 2 + dkv / 16 : 2 * dkv;
-  const int64_t code_off = (int64_t)bi * row_bytes + (KV4 ? kcol / 2 : 2 * kcol);
-  const int64_t sm_off = (int64_t)bi * row_bytes + dkv / 2 + (kcol / 64) * 4;
-  const auto load_kv = [&](const void* base, int p) -> h8 {
-    const char* row = static_cast<const char*>(base) + (int64_t)p * b * row_bytes;
-    if constexpr (KV4) {
-      h2 s2, m2;
-      scale_min_pairs(*reinterpret_cast<const uint32_t*>(row + sm_off), s2, m2);
-      return dequant8(*reinterpret_cast<const uint32_t*>(row + code_off), s2, m2);
-    } else {
-      return load_h8_stream(reinterpret_cast<const uint16_t*>(row + code_off));
-    }
+  const int64_t lane_off = (int64_t)bi * d + col;
+  const auto load_kv = [&](const uint16_t* base, int p) -> h8 {
+    return load_h8_stream(base + (int64_t)p * b * d + lane_off);
   };
   const auto visit = [&](h8 kv, h8 vv) {
-    float kf[8], vf[8];
+    float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      kf[i] = (float)kv[i];
-      vf[i] = (float)vv[i];
-    }
-    if constexpr (G == 1) {  // bound by HBM: the plain update (DPP sums measured no faster)
-      float s = 0.f;
+    for (int i = 0; i < 8; ++i) s += qf[i] * (float)kv[i];
+    // (bound by HBM: DPP sums measured no faster)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) s += qf[0][i] * kf[i];
+    for (int off = LPP / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    const float mn = fmaxf(m, s);
+    const float alpha = expf(m - mn);
+    const float e = expf(s - mn);
+    l = l * alpha + e;
 #pragma unroll
-      for (int off = LPP / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-      const float mn = fmaxf(m[0], s);
-      const float alpha = expf(m[0] - mn);
-      const float e = expf(s - mn);
-      l[0] = l[0] * alpha + e;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[0][i] = acc[0][i] * alpha + e * vf[i];
-      m[0] = mn;
-    } else {  // G query heads per key: bound by arithmetic
-      float alpha[G], e[G];
-      bool grew = false;
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s += qf[g][i] * kf[i];
-        s = group_sum<LPP>(s);
-        const float mn = fmaxf(m[g], s);
-        // hardware exp2; m = -inf on the first key gives alpha = 0
-        alpha[g] = __builtin_amdgcn_exp2f((m[g] - mn) * kLog2e);
-        e[g] = __builtin_amdgcn_exp2f((s - mn) * kLog2e);
-        l[g] = l[g] * alpha[g] + e[g];
-        grew |= alpha[g] != 1.f;
-        m[g] = mn;
-      }
-      // the running maxima rarely grow after the first keys: rescale only
-      // when some lane's did (alpha = 1 exactly otherwise)
-      if (__any(grew)) {
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc[g][i] *= alpha[g];
-      }
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[g][i] += e[g] * vf[i];
-    }
+    for (int i = 0; i < 8; ++i) acc[i] = acc[i] * alpha + e * (float)vv[i];
+    m = mn;
   };
   for (int p = p0 + wave * PPW + sub; p < p1; p += 8 * PPW) {
     const int p2 = min(p + 4 * PPW, p1 - 1);
@@ -194,31 +119,24 @@ __global__ __launch_bounds__(256) void attn_decode_k(const uint16_t* __restrict_
   // merge the lane groups of the wave (butterfly over the group index)
 #pragma unroll
   for (int off = LPK; off < 64; off <<= 1) {
+    float acc2[8];
+    const float m2 = __shfl_xor(m, off, 64);
+    const float l2 = __shfl_xor(l, off, 64);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float acc2[8];
-      const float m2 = __shfl_xor(m[g], off, 64);
-      const float l2 = __shfl_xor(l[g], off, 64);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc2[i] = __shfl_xor(acc[g][i], off, 64);
-      online_merge(m[g], l[g], acc[g], m2, l2, acc2);
-    }
+    for (int i = 0; i < 8; ++i) acc2[i] = __shfl_xor(acc[i], off, 64);
+    online_merge(m, l, acc, m2, l2, acc2);
   }
   if (sub == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int j = hl * G + g;  // query head within the workgroup
-      if (cd == 0) {
-        wm[wave][j] = m[g];
-        wl[wave][j] = l[g];
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) wacc[wave][j * D + cd + i] = acc[g][i];
+    if (cd == 0) {
+      wm[wave][hl] = m;
+      wl[wave][hl] = l;
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) wacc[wave][hl * D + cd + i] = acc[i];
   }
   __syncthreads();
-  for (int c = tid; c < NQ * D; c += 256) {
-    const int j = c / D, cc = c % D, h = kb * NQ + j;
+  for (int c = tid; c < HP * D; c += 256) {
+    const int j = c / D, cc = c % D, h = kb * HP + j;
     float M = wm[0][j], L = wl[0][j], A = wacc[0][c];
 #pragma unroll
     for (int w = 1; w < 4; ++w) {
@@ -243,7 +161,7 @@ __global__ __launch_bounds__(256) void attn_decode_k(const uint16_t* __restrict_
   }
 }
 
-// decode over an INT4 cache without grouping (G = 1): the same structure
+// decode over an INT4 cache without grouping: the same structure
 // as attn_decode_k, but a lane holds 32 elements of a key's head (one
 // 16-byte load of codes and one (scale, min) pair instead of four 4-byte
 // loads for 8 elements each), so a wave issues a quarter of the load
@@ -426,40 +344,6 @@ __global__ __launch_bounds__(D) void attn_decode_combine(const float* __restrict
 constexpr int kPQ = 128;  // queries per workgroup
 constexpr int kPK = 64;   // keys per block
 constexpr int kPrefillStages = 2;
-
-// LDS slot of 16-byte chunk `chunk` of key row `key` (an involution: the
-// DMA puts cache chunk kv_swz(row, s) into slot s, a read of chunk c goes
-// to slot kv_swz(row, c)).  The chunk is XORed with a mask that depends on
-// the row's low four bits, chosen with the LDS bank-conflict counters: over
-// the K fragment reads (ds_read_b128; lane r + 16 g reads row r of a 16-row
-// group, chunk 4 kk + g) and the transposed V reads (ds_read_b64_tr_b16;
-// rows 4 g .. 4 g + 3 of a group, chunks 2 n and 2 n + 1), a plain XOR with
-// the row leaves the K reads conflict-free but gives every V read a 2-way
-// conflict, the row rotated left by one bit the reverse, and of 240 random
-// masks that clear the V reads three cleared the K reads as well; the table
-// below is the first of them (head_dim 128: 16 chunks per row).  For
-// head_dim 64 (two rows per 256 bytes) the mask row & 6 measured no
-// conflicts on either read.
-template <int D>
-__device__ __forceinline__ int kv_swz(int key, int chunk) {
-  if constexpr (D == 128) {
-    constexpr uint64_t kMask = 0x618d34ea5b2f0c97ull;  // nibble x: mask of rows with key % 16 == x
-    return chunk ^ (int)((kMask >> (4 * (key & 15))) & 15);
-  } else {
-    return chunk ^ (key & 6);
-  }
-}
-
-// the pair of values that v_permlane16/32_swap leave in a lane: its own
-// and that of the lane 16 (32) apart, in either order
-template <typename P>
-__device__ __forceinline__ float pair_max(P p) {
-  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-template <typename P>
-__device__ __forceinline__ float pair_sum(P p) {
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
 
 template <int NS, int DMA>
 __device__ __forceinline__ void wait_blocks_landed(int pending) {
@@ -700,6 +584,17 @@ int attn_decode_splits(int b, int n_heads, int n_kv_heads, int t, bool kv4) {
   // at least kAttnDecodeMinWGs workgroups (three per CU: fewer leave HBM
   // idle, more only add merge traffic), at least 64 keys per split
   const int T = t + 1;
+  if (n_heads != n_kv_heads) {
+    // grouped: a workgroup's eight waves already share its keys, so splits
+    // only where they fill the chip and keep 512 keys each, up to 8 (2048 each
+    // beyond: merging more costs more than it gains; b 1, 8000 keys: 14.8 us
+    // with 8, 15.9 with 16)
+    const int fill = (int)std::max<int64_t>(1, 256 / ((int64_t)b * n_kv_heads));
+    const int keys = std::max(std::min(T / 512, 8), std::min(T / 2048, kAttnDecodeMaxSplits));
+    const int S = std::max(1, std::min(fill, keys));
+    const int chunk = (T + S - 1) / S;
+    return (T + chunk - 1) / chunk;
+  }
   const int wgs = b * (n_kv_heads / attn_decode_heads_per_wg(b, n_heads, n_kv_heads, kv4));
   int S = (kAttnDecodeMinWGs + wgs - 1) / wgs;
   S = std::min(S, std::max(1, T / 64));
@@ -712,52 +607,40 @@ int64_t attn_decode_workspace_bytes(int b, int n_heads, int head_dim, int splits
   return splits > 1 ? (int64_t)b * n_heads * splits * (head_dim + 2) * 4 : 0;
 }
 
-template <int D, int G, int HP, bool KV4>
-static void launch_decode_g(const uint16_t* q, const void* kc, const void* vc, uint16_t* o,
-                            int b, int Hkv, int t, int S, int chunk, float* workspace,
-                            hipStream_t st) {
-  const dim3 grid((unsigned)(Hkv / HP), (unsigned)b, (unsigned)S);
-  launch(attn_decode_k<D, G, HP, KV4>, grid, dim3(256), 0, st, q, kc, vc, o, workspace, b, Hkv,
-         t, chunk);
+template <int D>
+static void launch_decode_combine(const float* workspace, uint16_t* o, int b, int H, int S,
+                                  hipStream_t st) {
   if (S > 1)
-    launch(attn_decode_combine<D>, dim3((unsigned)(Hkv * G), (unsigned)b), dim3(D), 0, st,
-           (const float*)workspace, o, Hkv * G, S);
+    launch(attn_decode_combine<D>, dim3((unsigned)H, (unsigned)b), dim3(D), 0, st, workspace, o, H,
+           S);
 }
 
 template <int D, int HP>
-static void launch_decode_kv4(const uint16_t* q, const void* kc, const void* vc, uint16_t* o,
-                              int b, int H, int t, int S, int chunk, float* workspace,
+static void launch_decode_mha(const uint16_t* q, const void* kc, const void* vc, uint16_t* o,
+                              int b, int H, int t, bool kv4, int S, int chunk, float* workspace,
                               hipStream_t st) {
   const dim3 grid((unsigned)(H / HP), (unsigned)b, (unsigned)S);
-  launch(attn_decode_kv4_k<D, HP>, grid, dim3(256), 0, st, q, kc, vc, o, workspace, b, H, t,
-         chunk);
-  if (S > 1)
-    launch(attn_decode_combine<D>, dim3((unsigned)H, (unsigned)b), dim3(D), 0, st,
-           (const float*)workspace, o, H, S);
+  if (kv4)
+    launch(attn_decode_kv4_k<D, HP>, grid, dim3(256), 0, st, q, kc, vc, o, workspace, b, H, t,
+           chunk);
+  else
+    launch(attn_decode_k<D, HP>, grid, dim3(256), 0, st, q, static_cast<const uint16_t*>(kc),
+           static_cast<const uint16_t*>(vc), o, workspace, b, H, t, chunk);
 }
 
-template <int D, bool KV4>
+template <int D>
 static void launch_decode_d(const uint16_t* q, const void* kc, const void* vc, uint16_t* o, int b,
-                            int Hkv, int G, int HP, int t, int S, int chunk, float* workspace,
-                            hipStream_t st) {
-  if constexpr (KV4) {  // INT4 rows without grouping: 32 elements per lane
-    if (G == 1) {
-      if (HP == 4) return launch_decode_kv4<D, 4>(q, kc, vc, o, b, Hkv, t, S, chunk, workspace, st);
-      if (HP == 2) return launch_decode_kv4<D, 2>(q, kc, vc, o, b, Hkv, t, S, chunk, workspace, st);
-      return launch_decode_kv4<D, 1>(q, kc, vc, o, b, Hkv, t, S, chunk, workspace, st);
-    }
-  }
-#define PIPO_DECODE_CASE(g, hp)                                                         \
-  if (G == g && HP == hp)                                                               \
-    return launch_decode_g<D, g, hp, KV4>(q, kc, vc, o, b, Hkv, t, S, chunk, workspace, \
-                                          st);
-  PIPO_DECODE_CASE(1, 4)
-  PIPO_DECODE_CASE(1, 2)
-  PIPO_DECODE_CASE(1, 1)
-  PIPO_DECODE_CASE(2, 1)
-  PIPO_DECODE_CASE(4, 1)
-  PIPO_DECODE_CASE(8, 1)
-#undef PIPO_DECODE_CASE
+                            int Hkv, int G, int HP, int t, bool kv4, int S, int chunk,
+                            float* workspace, hipStream_t st) {
+  if (G > 1)
+    launch_decode_gqa(q, kc, vc, o, b, Hkv, G, D, t, kv4, S, chunk, workspace, st);
+  else if (HP == 4)
+    launch_decode_mha<D, 4>(q, kc, vc, o, b, Hkv, t, kv4, S, chunk, workspace, st);
+  else if (HP == 2)
+    launch_decode_mha<D, 2>(q, kc, vc, o, b, Hkv, t, kv4, S, chunk, workspace, st);
+  else
+    launch_decode_mha<D, 1>(q, kc, vc, o, b, Hkv, t, kv4, S, chunk, workspace, st);
+  launch_decode_combine<D>(workspace, o, b, Hkv * G, S, st);
 }
 
 static pipo_status check_heads(const char* what, int n_heads, int n_kv_heads, int head_dim) {
@@ -801,12 +684,8 @@ pipo_status launch_attn_decode(const uint16_t* q, const void* kc, const void* vc
   if (!workspace || workspace_bytes < attn_decode_workspace_bytes(b, n_heads, head_dim, S)) S = 1;
   const int chunk = (T + S - 1) / S;
   S = (T + chunk - 1) / chunk;
-  if (head_dim == 128)
-    (kv4 ? launch_decode_d<128, true> : launch_decode_d<128, false>)(
-        q, kc, vc, o, b, n_kv_heads, G, HP, t, S, chunk, workspace, st);
-  else
-    (kv4 ? launch_decode_d<64, true> : launch_decode_d<64, false>)(
-        q, kc, vc, o, b, n_kv_heads, G, HP, t, S, chunk, workspace, st);
+  (head_dim == 128 ? launch_decode_d<128> : launch_decode_d<64>)(
+      q, kc, vc, o, b, n_kv_heads, G, HP, t, kv4, S, chunk, workspace, st);
   PIPO_HIP_TRY(hipGetLastError());
   return PIPO_OK;
 }

@@ -1,0 +1,276 @@
+// Grouped-query decode attention on the matrix cores: one new query per
+// (sequence, head) against keys 0..t, the G query heads of a key/value head
+// as columns of 16 x 16 products.
+//
+// A workgroup is W waves on one (sequence, key/value head, split); each wave
+// takes a contiguous share of the split's keys, 32 at a time, through LDS of
+// its own (no barrier in the key loop).  fp16 rows come straight from the
+// cache by the load unit, INT4 rows through registers, where they are
+// expanded; both are laid out as in attn_prefill_k (kv_swz), so the two cache
+// formats run the same arithmetic.  The wave computes S^T = K Q^T (keys on
+// the rows, heads on the columns, so a lane holds scores of one head), an
+// online softmax per head in fp32, and O^T += V^T P^T with V^T read by
+// transposed LDS reads in the key order that S^T left P in.  P goes to the
+// product as the sum of two fp16 values, hi = fp16(p) and lo = fp16(p - hi),
+// which keeps 22 of its bits.  Waves are merged in order through LDS, splits
+// by attn_decode_combine.
+//
+// Bound by HBM and the fixed cost of a launch.  The kernel it replaced did
+// the G dot products and accumulator updates on the vector units, about 150
+// instructions for 4 keys, where 32 keys now take about 170; and it needed
+// more, smaller workgroups, so more splits to merge.  us with the merge, fp16
+// (INT4): b 16, 32/8 heads of 128, 544 keys 18.3 -> 9.9 (19.9 -> 11.0); b 128,
+// 64/8 heads 109 -> 60 (4.7 TB/s); b 16, 64/8 heads, 4096 keys 105 -> 54 (114
+// -> 45); b 1, 32/8 heads, 8000 keys 30 -> 15.
+#include "attention_common.h"
+
+namespace pipo {
+
+constexpr int kGqaKeys = 32;  // keys of a block
+
+// Eight waves (128 KiB of LDS at head_dim 128, one workgroup per CU) while
+// that gives every workgroup a CU, else four, two workgroups per CU, so that
+// one's loads run beside the other's products (b 64, 8 key/value heads, 544
+// keys: 32.9 us with eight, 30.8 with four; b 16: 9.9 and 11.9).
+constexpr int kGqaWideWGs = 256;
+
+// DIRECT: fp16 rows by global -> LDS loads (16-byte aligned cache), else
+// through registers
+template <int D, int W, bool KV4, bool DIRECT>
+__global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
+    const uint16_t* __restrict__ q, const void* __restrict__ kc, const void* __restrict__ vc,
+    uint16_t* __restrict__ o, float* __restrict__ part, int b, int Hkv, int G, int t, int chunk) {
+  constexpr int ROWB = 2 * D, BLK = kGqaKeys * ROWB;  // bytes of a key row, of K (or V) per block
+  constexpr int DMA = BLK / 1024, RPD = 1024 / ROWB;  // loads of a block, rows per load
+  constexpr int KK = D / 32, NF = D / 16;
+  constexpr float kLog2e = 1.4426950408889634f;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[W * 2 * BLK];
+  __shared__ float wm[W][8], wl[W][8];
+  const int kh = blockIdx.x, bi = blockIdx.y, sp = blockIdx.z, S = gridDim.z;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int H = Hkv * G, T = t + 1;
+  const int64_t d = (int64_t)H * D, dkv = (int64_t)Hkv * D;
+  // this wave's keys [p0, p1): the split's keys in W contiguous shares
+  const int s0 = sp * chunk, s1 = min(T, s0 + chunk);
+  const int share = (s1 - s0 + W - 1) / W;
+  const int p0 = s0 + wave * share, p1 = min(s1, p0 + share);
+  uint8_t* const kl = lds + wave * (2 * BLK);
+  uint8_t* const vl = kl + BLK;
+
+  // Q^T (B operand): lane (r, g) holds head r, dims 32 kk + 8 g ..; the
+  // columns past G are zero and never stored
+  h8 qf[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk)
+    qf[kk] = r < G ? load_h8(q + (int64_t)bi * d + (int64_t)(kh * G + r) * D + 32 * kk + 8 * g)
+                   : zero_h8();
+
+  const int64_t row_bytes = KV4 ? dkv / 2 + dkv / 16 : 2 * dkv;
+  const int64_t pos_bytes = (int64_t)b * row_bytes;  // between positions
+  const char* const kbase = static_cast<const char*>(kc) + (int64_t)bi * row_bytes;
+  const char* const vbase = static_cast<const char*>(vc) + (int64_t)bi * row_bytes;
+
+  // fp16: block at position p into LDS, rows past the share repeat its last
+  const int drow = lane / (ROWB / 16);
+  const auto issue = [&](const char* base, uint8_t* dst, int p) {
+    h8 x[DIRECT ? 1 : DMA];
+#pragma unroll
+    for (int i = 0; i < DMA; ++i) {
+      const int row = i * RPD + drow;
+      const int c = kv_swz<D>(row, lane % (ROWB / 16));
+      const char* src =
+          base + (int64_t)min(p + row, p1 - 1) * pos_bytes + (int64_t)kh * ROWB + 16 * c;
+      if constexpr (DIRECT)
+        lds_dma16(src, dst + i * 1024);
+      else
+        x[i] = load_h8(reinterpret_cast<const uint16_t*>(src));
+    }
+    if constexpr (!DIRECT) {
+#pragma unroll
+      for (int i = 0; i < DMA; ++i) *reinterpret_cast<h8*>(dst + i * 1024 + lane * 16) = x[i];
+    }
+  };
+  // INT4: 32 elements (one 16-byte word of codes, one pair) per lane and pass
+  constexpr int LPR = D / 32, PASS = kGqaKeys * LPR / 64;  // lanes per row, passes
+  struct Codes {
+    u32x4 c[PASS];
+    uint32_t sm[PASS];
+  };
+  const auto load4 = [&](const char* base, int p) {
+    Codes x;
+#pragma unroll
+    for (int i = 0; i < PASS; ++i) {
+      const int row = i * (64 / LPR) + lane / LPR, e = 32 * (lane % LPR);
+      const char* src = base + (int64_t)min(p + row, p1 - 1) * pos_bytes;
+      x.c[i] = *reinterpret_cast<const u32x4*>(src + ((int64_t)kh * D + e) / 2);
+      x.sm[i] = *reinterpret_cast<const uint32_t*>(src + dkv / 2 + ((int64_t)kh * D + e) / 64 * 4);
+    }
+    return x;
+  };
+  const auto expand4 = [&](const Codes& x, uint8_t* dst) {
+#pragma unroll
+    for (int i = 0; i < PASS; ++i) {
+      const int row = i * (64 / LPR) + lane / LPR;
+      h2 s2, m2;
+      scale_min_pairs(x.sm[i], s2, m2);
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        *reinterpret_cast<h8*>(dst + row * ROWB + 16 * kv_swz<D>(row, 4 * (lane % LPR) + w)) =
+            dequant8_fp8(x.c[i][w], s2, m2);
+    }
+  };
+
+  f4 oacc[NF];
+#pragma unroll
+  for (int n = 0; n < NF; ++n) oacc[n] = f4{0.f, 0.f, 0.f, 0.f};
+  float mrow = -INFINITY, lrow = 0.f;
+  Codes ck, cv;
+  if constexpr (KV4) {
+    if (p0 < p1) {
+      ck = load4(kbase, p0);
+      cv = load4(vbase, p0);
+    }
+  }
+  for (int p = p0; p < p1; p += kGqaKeys) {
+    if constexpr (KV4) {
+      expand4(ck, kl);
+      expand4(cv, vl);
+      if (p + kGqaKeys < p1) {  // the next block's codes travel beside this block's products
+        ck = load4(kbase, p + kGqaKeys);
+        cv = load4(vbase, p + kGqaKeys);
+      }
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
+    } else {
+      issue(kbase, kl, p);
+      issue(vbase, vl, p);
+      __builtin_amdgcn_s_waitcnt(DIRECT ? waitcnt_imm(DMA, false)  // K landed
+                                        : waitcnt_imm(63, true));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // s[j][e]: score of key p + 16 j + 4 g + e for head r
+    f4 s[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      s[j] = f4{0.f, 0.f, 0.f, 0.f};
+      const int row = 16 * j + r;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+        s[j] = mfma16(*reinterpret_cast<const h8*>(kl + row * ROWB + 16 * kv_swz<D>(row, 4 * kk + g)),
+                      qf[kk], s[j]);
+    }
+    if (p + kGqaKeys > p1) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (p + 16 * j + 4 * g + e >= p1) s[j][e] = -INFINITY;
+    }
+    float bm = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    bm = pair_max(__builtin_amdgcn_permlane16_swap(__float_as_uint(bm), __float_as_uint(bm), false, false));
+    bm = pair_max(__builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false));
+    const float mnew = fmaxf(mrow, bm);  // finite: every block has a key
+    const float alpha = __builtin_amdgcn_exp2f((mrow - mnew) * kLog2e);
+    mrow = mnew;
+    float rs = 0.f;
+    h8 hi, lo;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = __builtin_amdgcn_exp2f((s[j][e] - mnew) * kLog2e);
+        rs += x;
+        hi[4 * j + e] = (_Float16)x;
+        lo[4 * j + e] = (_Float16)(x - (float)hi[4 * j + e]);
+      }
+    rs = pair_sum(__builtin_amdgcn_permlane16_swap(__float_as_uint(rs), __float_as_uint(rs), false, false));
+    rs = pair_sum(__builtin_amdgcn_permlane32_swap(__float_as_uint(rs), __float_as_uint(rs), false, false));
+    lrow = lrow * alpha + rs;
+    if (__any(alpha != 1.f)) {  // the running maxima rarely grow after the first blocks
+#pragma unroll
+      for (int n = 0; n < NF; ++n) oacc[n] *= alpha;
+    }
+    if constexpr (!KV4 && DIRECT) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));  // V landed
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < NF; ++n) {
+      h8 vf;
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const int row = 16 * half + 4 * g + (r >> 2), dim = 16 * n + 4 * (r & 3);
+        const h4 x = lds_read_tr16(vl + row * ROWB + 16 * kv_swz<D>(row, dim / 8) + 2 * (dim % 8));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vf[4 * half + e] = x[e];
+      }
+      oacc[n] = mfma16(vf, hi, oacc[n]);
+      oacc[n] = mfma16(vf, lo, oacc[n]);
+    }
+    // this block's LDS is read
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // merge the waves: oacc[n][e] is dim 16 n + 4 g + e of head r
+  float* const wacc = reinterpret_cast<float*>(lds + wave * (2 * BLK));  // [G][D]
+  if (r < G) {
+    if (g == 0) {
+      wm[wave][r] = mrow;
+      wl[wave][r] = lrow;
+    }
+#pragma unroll
+    for (int n = 0; n < NF; ++n) *reinterpret_cast<f4*>(wacc + r * D + 16 * n + 4 * g) = oacc[n];
+  }
+  __syncthreads();
+  for (int c = tid; c < G * D; c += W * 64) {
+    const int j = c / D, cc = c % D, h = kh * G + j;
+    float M = wm[0][j];
+#pragma unroll
+    for (int w = 1; w < W; ++w) M = fmaxf(M, wm[w][j]);
+    float L = 0.f, A = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {  // a share may be empty (its maximum -inf)
+      const float a = __builtin_amdgcn_exp2f((wm[w][j] - M) * kLog2e);
+      L += wl[w][j] * a;
+      A += reinterpret_cast<const float*>(lds + w * (2 * BLK))[c] * a;
+    }
+    if (S == 1) {
+      o[(int64_t)bi * d + (int64_t)h * D + cc] = f2h(A / L);
+    } else {
+      float* pp = part + (((int64_t)bi * H + h) * S + sp) * (D + 2);
+      pp[cc] = A;
+      if (cc == 0) {
+        pp[D] = M;
+        pp[D + 1] = L;
+      }
+    }
+  }
+}
+
+template <int D, bool KV4, bool DIRECT>
+static void launch_gqa_d(const uint16_t* q, const void* kc, const void* vc, uint16_t* o, int b,
+                         int Hkv, int G, int t, int S, int chunk, float* part, hipStream_t st) {
+  const dim3 grid((unsigned)Hkv, (unsigned)b, (unsigned)S);
+  if ((int64_t)b * Hkv * S <= kGqaWideWGs)
+    launch(attn_decode_gqa_k<D, 8, KV4, DIRECT>, grid, dim3(512), 0, st, q, kc, vc, o, part, b,
+           Hkv, G, t, chunk);
+  else
+    launch(attn_decode_gqa_k<D, 4, KV4, DIRECT>, grid, dim3(256), 0, st, q, kc, vc, o, part, b,
+           Hkv, G, t, chunk);
+}
+
+void launch_decode_gqa(const uint16_t* q, const void* kc, const void* vc, uint16_t* o, int b,
+                       int Hkv, int G, int head_dim, int t, bool kv4, int S, int chunk,
+                       float* part, hipStream_t st) {
+  const bool direct = (reinterpret_cast<uintptr_t>(kc) | reinterpret_cast<uintptr_t>(vc)) % 16 == 0;
+  const auto go = [&](auto kernel) { kernel(q, kc, vc, o, b, Hkv, G, t, S, chunk, part, st); };
+  if (head_dim == 128)
+    go(kv4 ? launch_gqa_d<128, true, true>
+           : (direct ? launch_gqa_d<128, false, true> : launch_gqa_d<128, false, false>));
+  else
+    go(kv4 ? launch_gqa_d<64, true, true>
+           : (direct ? launch_gqa_d<64, false, true> : launch_gqa_d<64, false, false>));
+}
+
+}  // namespace pipo
