@@ -131,7 +131,7 @@ pipo_status pipo_op_attn_decode_noalloc(const uint16_t* q, const uint16_t* kc,
 
 /* The same over an INT4 KV cache (PIPO_KV_INT4_G64 rows of 9d/16 bytes,
  * position-major like the fp16 cache; d % 256 == 0): every key and value
- * is read as code * scale + min (rounded once to fp16).  Same workspace. */
+ * is read as code * scale + min, in fp32.  Same workspace. */
 pipo_status pipo_op_attn_decode_kv4(const uint16_t* q, const uint8_t* kc, const uint8_t* vc,
                                     uint16_t* o, int32_t b, int32_t n_heads, int32_t head_dim,
                                     int32_t t, void* workspace, int64_t workspace_bytes,

@@ -161,16 +161,25 @@ __global__ __launch_bounds__(256) void attn_decode_k(const uint16_t* __restrict_
   }
 }
 
-// decode over an INT4 cache without grouping: the same structure
-// as attn_decode_k, but a lane holds 32 elements of a key's head (one
-// 16-byte load of codes and one (scale, min) pair instead of four 4-byte
-// loads for 8 elements each), so a wave issues a quarter of the load
-// instructions per byte; D/32 lanes per head of a key.  The kernel is
-// bound by its arithmetic, so codes are expanded in pairs (k, k + 4) of
-// each group of 8 (one shift and mask per pair), q is held as fp16 pairs
-// in that order for two-element dot products (v_dot2_f32_f16), the
-// accumulators follow the same order until they are stored, and the
-// softmax uses the hardware exp2.
+// decode over an INT4 cache without grouping: the same structure as
+// attn_decode_k, but a lane holds 32 elements of a key's head (one 16-byte
+// load of codes and one (scale, min) pair), D/32 lanes per head of a key.
+// The kernel is bound by its arithmetic.  A word's eight codes become fp16 by
+// the fp8 converter (a byte c is the fp8 number c 2^-9; the low and the high
+// nibbles of the word's bytes, two codes per conversion: elements (0, 2),
+// (4, 6), (1, 3), (5, 7)), and scale and min leave the inner loops: with one
+// pair per lane and key,
+//   q . k = scale (q . codes) + min sum(q)      (two-element dot products)
+//   O += p v = (p scale) codes + p min          (p min: one sum for the lane)
+// all in fp32 from exact codes, so no expanded value is rounded to fp16 (the
+// error against 64 bits falls with it: 4.9e-4 -> 2.1e-4 at b 128, 544 keys).
+// The softmax uses the hardware exp2 and the accumulators are rescaled only
+// when some lane's running maximum grew.  26 instructions for a word of key
+// and a word of value codes, where expanding both to fp16 took 48.  us at b
+// 128, 56 heads of 128, 544 keys, with the quantization of the step's rows:
+// 149.7 -> 145.8, and 127.7 with the workgroups of a sequence on one XCD
+// (about 115 for this kernel, of which the instructions issue for 82; the
+// cache alone is 88 at 6.4 TB/s).
 template <int D, int HP>
 __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restrict__ q,
                                                          const void* __restrict__ kc,
@@ -184,7 +193,14 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
   constexpr int PPW = 64 / LPK;      // keys per wave per pass
   __shared__ float wm[4][HP], wl[4][HP];
   __shared__ float wacc[4][HP * D];
-  const int kb = blockIdx.x, bi = blockIdx.y, sp = blockIdx.z, S = gridDim.z;
+  // XCD x (workgroups x, x + 8, ..) takes a contiguous range of (sequence,
+  // head group) pairs: the head groups of a sequence share the lines at their
+  // borders and those of the (scale, min) pairs, which then meet in one L2
+  const int groups = H / HP;
+  const int64_t pair = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  if (pair >= (int64_t)groups * b) return;
+  const int bi = (int)(pair / groups), kb = (int)(pair - (int64_t)bi * groups);
+  const int sp = blockIdx.y, S = gridDim.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane / LPK, cl = lane % LPK, hl = cl / LPP, cd = (cl % LPP) * EPL;
   const int64_t d = (int64_t)H * D;
@@ -193,16 +209,22 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
   const int64_t col = (int64_t)(kb * HP + hl) * D + cd;
 
   constexpr float kLog2e = 1.4426950408889634f;
-  // qh[4 j + u] = (q[8 j + u], q[8 j + u + 4]); acc[8 j + 2 u + h] is element
-  // 8 j + u + 4 h
+  // qh[4 j + u]: elements 8 j + kElem[2 u], 8 j + kElem[2 u + 1]; acc the same
+  // order
+  constexpr int kElem[8] = {0, 2, 4, 6, 1, 3, 5, 7};
   h2 qh[EPL / 2];
+  float qsum = 0.f;
 #pragma unroll
   for (int j = 0; j < EPL / 8; ++j) {
-    const h8 qi = interleave_h8(load_h8(q + (int64_t)bi * d + col + 8 * j));
+    const h8 qv = load_h8(q + (int64_t)bi * d + col + 8 * j);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) qh[4 * j + u] = h2{qi[2 * u], qi[2 * u + 1]};
+    for (int u = 0; u < 4; ++u) {
+      qh[4 * j + u] = h2{qv[kElem[2 * u]], qv[kElem[2 * u + 1]]};
+      qsum += (float)qv[kElem[2 * u]] + (float)qv[kElem[2 * u + 1]];
+    }
   }
-  float m = -INFINITY, l = 0.f, acc[EPL];
+  // the output is acc[i] + accm
+  float m = -INFINITY, l = 0.f, acc[EPL], accm = 0.f;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) acc[i] = 0.f;
 
@@ -218,18 +240,20 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
     return Row{*reinterpret_cast<const u32x4*>(row + code_off),
                *reinterpret_cast<const uint32_t*>(row + sm_off)};
   };
+  // pair u (0..3) of a word's codes as fp16
+  const auto codes2 = [](uint32_t w, int u) -> h2 {
+    const uint32_t n = (u < 2 ? w : w >> 4) & 0x0F0F0F0Fu;
+    return u & 1 ? __builtin_bit_cast(h2, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(n, 512.f, true))
+                 : __builtin_bit_cast(h2, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(n, 512.f, false));
+  };
   const auto visit = [&](const Row& kr, const Row& vr) {
-    h2 ks, km, vs, vm;
-    scale_min_pairs(kr.sm, ks, km);
-    scale_min_pairs(vr.sm, vs, vm);
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        s = __builtin_amdgcn_fdot2(
-            qh[4 * j + u], dequant_pair((kr.codes[j] >> (4 * u)) & 0x000F000Fu, ks, km), s, false);
-    s = group_sum<LPP>(s);
+        s = __builtin_amdgcn_fdot2(qh[4 * j + u], codes2(kr.codes[j], u), s, false);
+    s = group_sum<LPP>(s * h2f((uint16_t)kr.sm) + h2f((uint16_t)(kr.sm >> 16)) * qsum);
     const float mn = fmaxf(m, s);
     // m = -inf on the first key: exp2(-inf) = 0
     const float alpha = __builtin_amdgcn_exp2f((m - mn) * kLog2e);
@@ -238,16 +262,19 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
     // the running maxima rarely grow after the first keys: rescale only
     // when some lane's did (alpha = 1 exactly otherwise)
     if (__any(alpha != 1.f)) {
+      accm *= alpha;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) acc[i] *= alpha;
     }
+    const float es = e * h2f((uint16_t)vr.sm);
+    accm += e * h2f((uint16_t)(vr.sm >> 16));
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const h2 vp = dequant_pair((vr.codes[j] >> (4 * u)) & 0x000F000Fu, vs, vm);
-        acc[8 * j + 2 * u] += e * (float)vp[0];
-        acc[8 * j + 2 * u + 1] += e * (float)vp[1];
+        const h2 c = codes2(vr.codes[j], u);
+        acc[8 * j + 2 * u] += es * (float)c[0];
+        acc[8 * j + 2 * u + 1] += es * (float)c[1];
       }
     m = mn;
   };
@@ -258,6 +285,8 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
     visit(ka, va);
     if (p + 4 * PPW < p1) visit(kb2, vb2);
   }
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) acc[i] += accm;
   // merge the key slots of the wave, then the waves through LDS
 #pragma unroll
   for (int off = LPK; off < 64; off <<= 1) {
@@ -278,7 +307,7 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
     }
 #pragma unroll
     for (int i = 0; i < EPL; ++i)
-      wacc[wave][hl * D + cd + 8 * (i / 8) + (i % 8) / 2 + 4 * (i % 2)] = acc[i];
+      wacc[wave][hl * D + cd + 8 * (i / 8) + kElem[i % 8]] = acc[i];
   }
   __syncthreads();
   for (int c = tid; c < HP * D; c += 256) {
@@ -620,8 +649,9 @@ static void launch_decode_mha(const uint16_t* q, const void* kc, const void* vc,
                               int b, int H, int t, bool kv4, int S, int chunk, float* workspace,
                               hipStream_t st) {
   const dim3 grid((unsigned)(H / HP), (unsigned)b, (unsigned)S);
+  const dim3 grid4((unsigned)(((int64_t)(H / HP) * b + 7) / 8 * 8), (unsigned)S);
   if (kv4)
-    launch(attn_decode_kv4_k<D, HP>, grid, dim3(256), 0, st, q, kc, vc, o, workspace, b, H, t,
+    launch(attn_decode_kv4_k<D, HP>, grid4, dim3(256), 0, st, q, kc, vc, o, workspace, b, H, t,
            chunk);
   else
     launch(attn_decode_k<D, HP>, grid, dim3(256), 0, st, q, static_cast<const uint16_t*>(kc),
