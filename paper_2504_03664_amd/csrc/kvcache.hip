@@ -8,73 +8,103 @@
 //                 code = clamp(rint((x - min) / scale), 0, 15), half to
 //                 even, 0 where scale is 0 (both divisions IEEE-rounded).
 //   kv_dequant_k: INT4 rows -> fp16 rows, code * scale + min rounded once.
-// One thread per group of 64: 128 bytes in, 36 out (or the reverse).
+// Eight lanes per group of 64, 8 elements each: a lane moves 16 bytes of fp16
+// and 4 of codes, so a wave's accesses are contiguous and a decode step's few
+// rows spread over the chip.  (One lane per group, 128 bytes and 64 divisions
+// in a row, took 6 us for 128 rows of 7168, about 2 more than a launch.)
 #include "common.h"
 #include "device.h"
 
 namespace pipo {
 
+// largest of the 8 lanes of a group, by DPP moves within a row of 16 lanes
+// (swap neighbours, swap pairs, mirror within 8)
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v) {
+  return __uint_as_float(
+      __builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float group_max8(float v) {
+  v = fmaxf(v, lane_move<0xB1>(v));
+  v = fmaxf(v, lane_move<0x4E>(v));
+  return fmaxf(v, lane_move<0x141>(v));
+}
+__device__ __forceinline__ float group_min8(float v) {
+  v = fminf(v, lane_move<0xB1>(v));
+  v = fminf(v, lane_move<0x4E>(v));
+  return fminf(v, lane_move<0x141>(v));
+}
+
+// row and 8-element piece of this thread; false past the end.  A row has a
+// multiple of 32 pieces, so the 8 lanes of a group are all in or all out.
+// The division is 32-bit where the pieces allow (64-bit took a third of the
+// quantizer's time).
+__device__ __forceinline__ bool piece_of(int64_t rows, int64_t d, int64_t& r, int& c) {
+  const int64_t per_row = d / 8, e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= rows * per_row) return false;
+  if (rows * per_row < ((int64_t)1 << 32)) {
+    const uint32_t row = (uint32_t)e / (uint32_t)per_row;
+    r = row;
+    c = (int)((uint32_t)e - row * (uint32_t)per_row);
+  } else {
+    r = e / per_row;
+    c = (int)(e - r * per_row);
+  }
+  return true;
+}
+
 __global__ __launch_bounds__(256) void kv_quant_k(const uint16_t* __restrict__ x,
                                                   uint8_t* __restrict__ out, int64_t rows,
                                                   int64_t d) {
-  const int64_t groups = d / 64;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= rows * groups) return;
-  const int64_t r = e / groups, gi = e % groups;
-  const uint16_t* src = x + r * d + gi * 64;
-  float v[64];
+  int64_t r;
+  int c;  // 8-element piece of row r
+  if (!piece_of(rows, d, r, c)) return;
+  const h8 h = load_h8(x + r * d + 8 * c);
+  float v[8], mn, mx;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const h8 h = load_h8(src + 8 * i);
+  for (int j = 0; j < 8; ++j) v[j] = (float)h[j];
+  mn = mx = v[0];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[8 * i + j] = (float)h[j];
+  for (int j = 1; j < 8; ++j) {
+    mn = fminf(mn, v[j]);
+    mx = fmaxf(mx, v[j]);
   }
-  float mn = v[0], mx = v[0];
-#pragma unroll
-  for (int i = 1; i < 64; ++i) {
-    mn = fminf(mn, v[i]);
-    mx = fmaxf(mx, v[i]);
-  }
+  mn = group_min8(mn);
+  mx = group_max8(mx);
   const _Float16 s16 = (_Float16)((mx - mn) / 15.f);
   const _Float16 m16 = (_Float16)mn;
   const float s = (float)s16, m = (float)m16;
-  u32x4 codes[2];
+  // (x - min) / scale, correctly rounded from the correctly rounded reciprocal
+  // and one residual step (Markstein, IBM J. Res. Dev. 34, 1990): an eighth of
+  // a division per element.  Infinite inputs give NaN and code 0, as the
+  // division would.
+  const float inv = s != 0.f ? 1.f / s : 0.f;
+  uint32_t word = 0;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    uint32_t word = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float c = 0.f;
-      if (s != 0.f) c = fminf(fmaxf(__builtin_rintf((v[8 * w + j] - m) / s), 0.f), 15.f);
-      word |= (uint32_t)c << (4 * j);
-    }
-    codes[w >> 2][w & 3] = word;
+  for (int j = 0; j < 8; ++j) {
+    const float x = v[j] - m, q0 = x * inv;
+    const float q = __builtin_fmaf(__builtin_fmaf(-q0, s, x), inv, q0);
+    word |= (uint32_t)(s != 0.f ? fminf(fmaxf(__builtin_rintf(q), 0.f), 15.f) : 0.f) << (4 * j);
   }
   uint8_t* row = out + r * (d / 2 + d / 16);
-  *reinterpret_cast<u32x4*>(row + gi * 32) = codes[0];
-  *reinterpret_cast<u32x4*>(row + gi * 32 + 16) = codes[1];
-  *reinterpret_cast<uint32_t*>(row + d / 2 + gi * 4) =
-      (uint32_t)__builtin_bit_cast(uint16_t, s16) | ((uint32_t)__builtin_bit_cast(uint16_t, m16) << 16);
+  *reinterpret_cast<uint32_t*>(row + 4 * c) = word;
+  if (c % 8 == 0)
+    *reinterpret_cast<uint32_t*>(row + d / 2 + c / 8 * 4) =
+        (uint32_t)__builtin_bit_cast(uint16_t, s16) |
+        ((uint32_t)__builtin_bit_cast(uint16_t, m16) << 16);
 }
 
 __global__ __launch_bounds__(256) void kv_dequant_k(const uint8_t* __restrict__ in,
                                                     uint16_t* __restrict__ y, int64_t rows,
                                                     int64_t d) {
-  const int64_t groups = d / 64;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= rows * groups) return;
-  const int64_t r = e / groups, gi = e % groups;
+  int64_t r;
+  int c;
+  if (!piece_of(rows, d, r, c)) return;
   const uint8_t* row = in + r * (d / 2 + d / 16);
-  const u32x4 c0 = *reinterpret_cast<const u32x4*>(row + gi * 32);
-  const u32x4 c1 = *reinterpret_cast<const u32x4*>(row + gi * 32 + 16);
+  const uint32_t codes = *reinterpret_cast<const uint32_t*>(row + 4 * c);
   h2 s2, m2;
-  scale_min_pairs(*reinterpret_cast<const uint32_t*>(row + d / 2 + gi * 4), s2, m2);
-  uint16_t* dst = y + r * d + gi * 64;
-#pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    const h8 h = dequant8(w < 4 ? c0[w] : c1[w - 4], s2, m2);
-    *reinterpret_cast<h8*>(dst + 8 * w) = h;
-  }
+  scale_min_pairs(*reinterpret_cast<const uint32_t*>(row + d / 2 + c / 8 * 4), s2, m2);
+  *reinterpret_cast<h8*>(y + r * d + 8 * c) = dequant8_fp8(codes, s2, m2);
 }
 
 pipo_status launch_kv_quant(const uint16_t* x, uint8_t* out, int64_t rows, int64_t d,
@@ -84,7 +114,7 @@ pipo_status launch_kv_quant(const uint16_t* x, uint8_t* out, int64_t rows, int64
               (long long)d);
     return PIPO_ERR_UNSUPPORTED;
   }
-  const int64_t n = rows * (d / 64);
+  const int64_t n = rows * (d / 8);
   if (n == 0) return PIPO_OK;
   launch(kv_quant_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, out, rows, d);
   PIPO_HIP_TRY(hipGetLastError());
@@ -98,7 +128,7 @@ pipo_status launch_kv_dequant(const uint8_t* in, uint16_t* y, int64_t rows, int6
               (long long)d);
     return PIPO_ERR_UNSUPPORTED;
   }
-  const int64_t n = rows * (d / 64);
+  const int64_t n = rows * (d / 8);
   if (n == 0) return PIPO_OK;
   launch(kv_dequant_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, in, y, rows, d);
   PIPO_HIP_TRY(hipGetLastError());
