@@ -95,7 +95,10 @@ def gemm_symbols(M, N, K, epi, w4, frag):
     if M <= 16:
         cfg = None
         if epi != 5 and not (w4 and epi == 0):   # (always the skinny kernel)
-            if 5120 <= N <= 8192 and (M > 8 or (not w4 and K >= 16384)):
+            if not w4 and not frag:
+                cfg = ((1, 1, 1, 8, 3) if N < 5120 else
+                       (1, 2, 1, 8, 2) if N <= 8192 else (1, 2, 2, 4, 2))
+            elif 5120 <= N <= 8192 and (M > 8 or (not w4 and K >= 16384)):
                 cfg = (1, 2, 1, 8, 4) if w4 else (1, 2, 1, 8, 2)
             elif N < 5120 and M > 8 and not w4:
                 cfg = (1, 1, 1, 8, 3)

@@ -899,7 +899,7 @@ static int split_k(int64_t wgs, int64_t K, int64_t kper_min) {
 
 // rows of the slab tables (gemm_common.h) by what they are for
 enum { kF16M16n16 = 0, kF16M16n32, kF16M32n32, kF16M32n96, kF16M32n128, kF16M64n64, kF16M64n96,
-       kF16M64n128, kF16M128n64, kF16M128n128 };
+       kF16M64n128, kF16M128n64, kF16M128n128, kF16M16n64 };
 enum { kW4M16n32 = 0, kW4M32n64, kW4M32n128, kW4M64n64, kW4M64n128, kW4M128n64, kW4M128n128,
        kW4M128n256, kW4M128n256k1 };
 
@@ -916,8 +916,16 @@ enum { kW4M16n32 = 0, kW4M32n64, kW4M32n128, kW4M64n64, kW4M64n128, kW4M128n64, 
 // both kernels give the same bits; with INT4 W an EPI_F16 output stays with
 // the skinny kernel: EPI_SWIGLU, which only that kernel has, gives the values
 // of EPI_F16 and the SwiGLU kernel bit for bit.
-static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi) {
+// Row-major fp16 W: the skinny kernel's loads take 64 bytes of each of 16
+// rows, half of every 128-byte line, the slab kernel's whole lines, so it is
+// the faster one at every M and N (M = 16: 128256 x 4096 224 -> 188, 50272 x
+// 7168 182 -> 126; M = 1: 5120 x 5120 19.2 -> 11.9, 4096 x 14336 26 -> 21), with
+// 64 columns above N = 8192.
+static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool packed) {
   if (w4 && epi == EPI_F16) return {kSkinny};
+  if (!w4 && !packed) {
+    return {kSlab, N < 5120 ? kF16M16n16 : (N <= 8192 ? kF16M16n32 : kF16M16n64)};
+  }
   const bool rows16 = M > 8, longk = !w4 && K >= 16384;
   if (N >= 5120 && N <= 8192 && (rows16 || longk))
     return {kSlab, w4 ? kW4M16n32 : kF16M16n32};
@@ -992,14 +1000,14 @@ static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4) {
   return {kBig, 0, S};
 }
 
-static GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool w4, int epi) {
-  if (M <= kSkinnyMaxM) return plan_m16(M, N, K, w4, epi);
+static GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool packed) {
+  if (M <= kSkinnyMaxM) return plan_m16(M, N, K, w4, epi, packed);
   return M <= kDecodeMaxM ? plan_decode(M, N, K, w4) : plan_prefill(M, N, K, w4);
 }
 
 int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4) {
   if (M <= kSkinnyMaxM || N <= 0 || K <= 0 || K % 128 != 0) return 0;
-  const GemmPlan p = gemm_plan(M, N, K, w4, EPI_F32);  // (no epilogue changes a split)
+  const GemmPlan p = gemm_plan(M, N, K, w4, EPI_F32, true);  // the splits of every call
   return p.splits > 1 ? (int64_t)p.splits * M * N * 4 : 0;
 }
 
@@ -1043,7 +1051,7 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
     PIPO_HIP_TRY(hipGetLastError());
     return PIPO_OK;
   } else {
-    GemmPlan p = gemm_plan(a.M, a.N, a.K, W4, EPI);
+    GemmPlan p = gemm_plan(a.M, a.N, a.K, W4, EPI, PK);
     // as many of the planned K ranges as the workspace has room for
     while (p.splits > 1 && (ws == nullptr || a.M * a.N >= ((int64_t)1 << 31) ||
                             ws_bytes < (int64_t)p.splits * a.M * a.N * 4))

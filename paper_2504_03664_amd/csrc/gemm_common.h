@@ -129,7 +129,8 @@ void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStrea
   X(0, 1, 1, 1, 8, 3) X(1, 1, 2, 1, 8, 2)                                               \
   X(2, 2, 1, 2, 4, 3) X(3, 2, 3, 2, 2, 3) X(4, 2, 2, 4, 2, 2)                           \
   X(5, 4, 1, 4, 2, 3) X(6, 4, 3, 2, 2, 2) X(7, 4, 1, 8, 1, 3)                           \
-  X(8, 8, 1, 4, 2, 2) X(9, 8, 1, 8, 1, 3)
+  X(8, 8, 1, 4, 2, 2) X(9, 8, 1, 8, 1, 3)                                               \
+  X(10, 1, 2, 2, 4, 2)
 #define PIPO_SLAB_W4(X)                                                                 \
   X(0, 1, 2, 1, 8, 4)                                                                   \
   X(1, 2, 2, 2, 4, 3) X(2, 2, 2, 4, 4, 2)                                               \

@@ -89,14 +89,16 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
   const int64_t m0 = (tile - tn * tiles_m) * C::kRows;
   const int64_t nwg = tn * C::kCols, nw0 = nwg + wn * (16 * NF);
   const int64_t kbeg = (int64_t)blockIdx.y * kper;
-  // chunk of K group j in round t.  KS = 8 deals the chunks in pairs, 128 k to
-  // a group, as gemm_skinny deals its steps to its 8 waves: with fp16 W the
-  // two kernels sum in the same order (K, and so the chunk count, is even)
+  // chunk of K group j in round t.  MF = 1 deals the chunks in pairs, 128 k
+  // at a time, as gemm_skinny deals its steps to its 8 waves, and keeps 8
+  // partial sums (kSums of them in a wave), so with fp16 W the two kernels
+  // sum in the same order (K, and so the chunk count, is even)
+  constexpr int kSums = MF == 1 ? 8 / KS : 1;
   const auto chunk_of = [&](int t, int j) {
-    return KS == 8 ? 2 * (KS * (t >> 1) + j) + (t & 1) : KS * t + j;
+    return MF == 1 ? 2 * (KS * (t >> 1) + j) + (t & 1) : KS * t + j;
   };
   const int nch = (int)(kper / KC);
-  const int nr = KS == 8 ? 2 * ((nch / 2 + KS - 1) / KS) : (nch + KS - 1) / KS;
+  const int nr = MF == 1 ? 2 * ((nch / 2 + KS - 1) / KS) : (nch + KS - 1) / KS;
 
   // X: a load covers 8 rows x 64 k; rows past M repeat the last one, k past
   // the range the last 64 (loaded, never used)
@@ -172,13 +174,15 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
       for (int f = 0; f < 2 * NF; ++f) lds_dma16_w<NT>(wsrc[f] + k * 2, wb + f * 1024);
     }
   };
-  f4 acc[NF][MF];
+  f4 sums[kSums][NF][MF];
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
+  for (int u = 0; u < kSums; ++u)
 #pragma unroll
-    for (int mf = 0; mf < MF; ++mf) acc[f][mf] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int mf = 0; mf < MF; ++mf) sums[u][f][mf] = f4{0.f, 0.f, 0.f, 0.f};
   constexpr bool kPairs = W4 && MF < 8;
-  const auto compute = [&](int slot) {
+  const auto compute = [&](int slot, f4 (&acc)[NF][MF]) {
     // row r of a 16-row block of X (or row-major W), and where its chunk c is
     const int row_off = (r >> 3) * 1024 + (r & 7) * 128;
     const auto chunk = [&](int c) { return row_off + 16 * (c ^ ((r >> 1) & 7)); };
@@ -234,7 +238,12 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
     __builtin_amdgcn_s_barrier();              // everyone's did, and stage t - 1 is read
     __builtin_amdgcn_sched_barrier(0);
     if (t + PD < nr) issue(t + PD, slot == 0 ? PD : slot - 1);
-    if (chunk_of(t, ks) < nch) compute(slot);
+    if (chunk_of(t, ks) < nch) {
+      if (kSums == 2 && ((t >> 1) & 1))
+        compute(slot, sums[kSums - 1]);
+      else
+        compute(slot, sums[0]);
+    }
     slot = slot == PD ? 0 : slot + 1;
   }
 
@@ -269,26 +278,30 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
 #pragma unroll
     for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
-      for (int f = 0; f < NF; ++f) finish(nw0 + 16 * f, mf, acc[f][mf]);
+      for (int f = 0; f < NF; ++f) finish(nw0 + 16 * f, mf, sums[0][f][mf]);
   } else {
     // the K groups' sums meet in LDS, kPer fragments of every wave at a
     // time, and are added in group order, the fragments spread over the waves
-    constexpr int kFrags = NF * MF, kFit = C::kRing * C::kStage / 1024 / C::kWaves;
+    constexpr int kFrags = NF * MF, kFit = C::kRing * C::kStage / 1024 / C::kWaves / kSums;
     constexpr int kPer = kFit >= kFrags ? kFrags : (kFit >= kFrags / 2 ? kFrags / 2 : kFrags / 4);
+    static_assert(kSums <= 2, "MF = 1 needs KS of 4 or 8");
     static_assert(kPer >= 1 && kFrags % kPer == 0 && kPer <= kFit, "fragments fit LDS");
-    f4* red = reinterpret_cast<f4*>(lds);
+    f4* red = reinterpret_cast<f4*>(lds);  // [group][wn][kPer][lane], group kSums-major
 #pragma unroll
     for (int p0 = 0; p0 < kFrags; p0 += kPer) {
       __syncthreads();
 #pragma unroll
-      for (int e = 0; e < kPer; ++e)
-        red[(wave * kPer + e) * 64 + lane] = acc[(p0 + e) / MF][(p0 + e) % MF];
+      for (int u = 0; u < kSums; ++u)
+#pragma unroll
+        for (int e = 0; e < kPer; ++e)
+          red[((u * C::kWaves + wave) * kPer + e) * 64 + lane] =
+              sums[u][(p0 + e) / MF][(p0 + e) % MF];
       __syncthreads();
       for (int e = wave; e < WN * kPer; e += C::kWaves) {
         const int w = e / kPer, fr = e % kPer;
         f4 v = red[(w * kPer + fr) * 64 + lane];
 #pragma unroll
-        for (int k = 1; k < KS; ++k) v += red[((k * WN + w) * kPer + fr) * 64 + lane];
+        for (int k = 1; k < KS * kSums; ++k) v += red[((k * WN + w) * kPer + fr) * 64 + lane];
         finish(nwg + w * (16 * NF) + 16 * ((p0 + fr) / MF), (p0 + fr) % MF, v);
       }
     }
