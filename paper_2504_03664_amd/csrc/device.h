@@ -57,18 +57,12 @@ __device__ __forceinline__ void scale_min_pairs(uint32_t sm, h2& s2, h2& m2) {
   m2 = __builtin_bit_cast(h2, (sm >> 16) | (sm & 0xFFFF0000u));
 }
 
-__device__ __forceinline__ h2 dequant_pair(uint32_t t, h2 s2, h2 m2) {
-  const h2 c = __builtin_bit_cast(h2, t | 0x64006400u) - h2{(_Float16)1024.f, (_Float16)1024.f};
-  return __builtin_elementwise_fma(c, s2, m2);
-}
-
 // eight codes in the order (0, 4, 1, 5, 2, 6, 3, 7).  Codes 0 and 4 (bits
 // 0-3 and 16-19) go under the exponent of 1024 as above; codes 1 and 5
 // (bits 4-7 and 20-23) are left where they are, under the exponent of 64
 // (fp16 0x5400, spacing 1/16), where a code c at bits 4-7 reads as 64 + c:
 // one AND-OR per pair and one shift per word, no per-pair shifts.  The
-// biases 1024 and 64 are subtracted exactly before the fused multiply-add,
-// so the values are those of dequant_pair.
+// biases 1024 and 64 are subtracted exactly before the fused multiply-add.
 __device__ __forceinline__ h2 dequant_biased(uint32_t t, _Float16 bias, h2 s2, h2 m2) {
   const h2 c = __builtin_bit_cast(h2, t) - h2{bias, bias};
   return __builtin_elementwise_fma(c, s2, m2);
@@ -109,26 +103,14 @@ __device__ __forceinline__ h8 dequant8_interleaved(uint32_t v, h2 s2, h2 m2) {
   return out;
 }
 
-// eight codes in natural order
-__device__ __forceinline__ h8 dequant8(uint32_t v, h2 s2, h2 m2) {
-  h8 out;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint32_t b = v >> (8 * j);
-    const h2 w = dequant_pair((b & 0xFu) | ((b << 12) & 0xF0000u), s2, m2);
-    out[2 * j] = w[0];
-    out[2 * j + 1] = w[1];
-  }
-  return out;
-}
-
 // eight codes in natural order through the fp8 converter: a byte holding a
 // code c (0..15) reads as the fp8 (e4m3) number c * 2^-9, subnormal up to 7
 // and exact throughout, so one instruction turns two of them into fp16 with
 // the scale 2^9.  Per word: the bytes are spread to 16 bits (two permutes),
 // their two codes to a byte each (shift-or, mask), then four conversions and
-// four fused multiply-adds: 14 instructions and the values of dequant8,
-// where biased halves in natural order took 16.
+// four fused multiply-adds: 14 instructions, where biased halves in natural
+// order took 16 or more.  (INT4 prefill, big tiles: M = 8192, N x K = 20480 x
+// 5120 1574 -> 1527 us.)
 __device__ __forceinline__ h8 dequant8_fp8(uint32_t v, h2 s2, h2 m2) {
   h8 out;
 #pragma unroll

@@ -83,22 +83,15 @@ struct SkinnyStep {
   }
 
   __device__ __forceinline__ void mma(f4 (&acc)[NF][MF]) const {
-    // INT4: codes are expanded in the order (0, 4, 1, 5, ...) of each group
-    // of eight k; X is permuted to match
-    h8 xv[MF][4];
-#pragma unroll
-    for (int mf = 0; mf < MF; ++mf)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) xv[mf][i] = W4 ? interleave_h8(x[mf][i]) : x[mf][i];
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       h2 s2, m2;
       if constexpr (W4) scale_min_pairs(sm[f], s2, m2);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const h8 wv = W4 ? dequant8_interleaved(w[f][0][i], s2, m2) : __builtin_bit_cast(h8, w[f][i]);
+        const h8 wv = W4 ? dequant8_fp8(w[f][0][i], s2, m2) : __builtin_bit_cast(h8, w[f][i]);
 #pragma unroll
-        for (int mf = 0; mf < MF; ++mf) acc[f][mf] = mfma16(wv, xv[mf][i], acc[f][mf]);
+        for (int mf = 0; mf < MF; ++mf) acc[f][mf] = mfma16(wv, x[mf][i], acc[f][mf]);
       }
     }
   }
@@ -437,7 +430,7 @@ __global__ __launch_bounds__(kTThreads) void gemm_tiled(GemmArgs a) {
         h2 s2, m2;
         scale_min_pairs(smw, s2, m2);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rb[i] = dequant8(codes[i], s2, m2);
+        for (int i = 0; i < 4; ++i) rb[i] = dequant8_fp8(codes[i], s2, m2);
       } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) rb[i] = zero_h8();
@@ -723,7 +716,7 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_f16(GemmArgs a, float* par
 // and (scale, min) pairs of a stage reach LDS through the load unit one
 // stage ahead of X; at step t every thread expands 16 codes of stage t + 1
 // (W row tid / 2, k 16 (tid & 1) .. + 15) into two 16-byte fragment slots,
-// so each code is expanded once per 256 rows of X.  A stage is X 16 KiB,
+// (through the fp8 converter) so each code is expanded once per 256 rows of X.  A stage is X 16 KiB,
 // expanded W 16 KiB, codes 4 KiB, pairs 1 KiB; four stages, 148 KiB.
 template <int EPI, bool PK>
 __global__ __launch_bounds__(kFThreads) void gemm_big_w4(GemmArgs a) {
@@ -784,8 +777,8 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_w4(GemmArgs a) {
     h2 s2, m2;
     scale_min_pairs(sm, s2, m2);
     uint8_t* wb = st + WOFF + (row >> 4) * 1024 + ((row & 15) + 32 * half) * 16;
-    *reinterpret_cast<h8*>(wb) = dequant8(c[0], s2, m2);
-    *reinterpret_cast<h8*>(wb + 256) = dequant8(c[1], s2, m2);
+    *reinterpret_cast<h8*>(wb) = dequant8_fp8(c[0], s2, m2);
+    *reinterpret_cast<h8*>(wb + 256) = dequant8_fp8(c[1], s2, m2);
   };
   const auto read = [&](int t, h8 (&fa)[FM], h8 (&fb)[FN]) {
     const uint8_t* st = lds + (t % kFStages) * STAGE;
