@@ -1,6 +1,8 @@
 // GEMM kernel of decode (M <= 128) and of prefill with few tiles.
 #pragma once
 
+#include <type_traits>
+
 #include "gemm_common.h"
 
 namespace pipo {
@@ -182,7 +184,8 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
 #pragma unroll
       for (int mf = 0; mf < MF; ++mf) sums[u][f][mf] = f4{0.f, 0.f, 0.f, 0.f};
   constexpr bool kPairs = W4 && MF < 8;
-  const auto compute = [&](int slot, f4 (&acc)[NF][MF]) {
+  const auto compute = [&](int slot, auto sum) {
+    constexpr int u = decltype(sum)::value;
     // row r of a 16-row block of X (or row-major W), and where its chunk c is
     const int row_off = (r >> 3) * 1024 + (r & 7) * 128;
     const auto chunk = [&](int c) { return row_off + 16 * (c ^ ((r >> 1) & 7)); };
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
                : *reinterpret_cast<const h8*>(
                      wb + f * 2048 + (PK ? i * 1024 + lane * 16 : chunk(4 * i + g)));
 #pragma unroll
-        for (int mf = 0; mf < MF; ++mf) acc[f][mf] = mfma16(wv, xv[mf], acc[f][mf]);
+        for (int mf = 0; mf < MF; ++mf) sums[u][f][mf] = mfma16(wv, xv[mf], sums[u][f][mf]);
       }
     }
   };
@@ -239,10 +242,14 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
     __builtin_amdgcn_sched_barrier(0);
     if (t + PD < nr) issue(t + PD, slot == 0 ? PD : slot - 1);
     if (chunk_of(t, ks) < nch) {
-      if (kSums == 2 && ((t >> 1) & 1))
-        compute(slot, sums[kSums - 1]);
-      else
-        compute(slot, sums[0]);
+      if constexpr (kSums == 2) {
+        if ((t >> 1) & 1)
+          compute(slot, std::integral_constant<int, kSums - 1>{});
+        else
+          compute(slot, std::integral_constant<int, 0>{});
+      } else {
+        compute(slot, std::integral_constant<int, 0>{});
+      }
     }
     slot = slot == PD ? 0 : slot + 1;
   }
