@@ -358,10 +358,10 @@ __global__ __launch_bounds__(D) void attn_decode_combine(const float* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// prefill (flash-style): a workgroup owns 128 queries of one head and
-// sequence, 4 waves x 32 queries (two sub-blocks of 16).  Keys come in
-// blocks of 64, K and V moved from the cache straight into LDS by the load
-// unit (double-buffered), rows stored with their 16-byte chunks permuted by
+// prefill (flash-style): a workgroup owns 32 NW queries of one head and
+// sequence, NW waves x 32 queries (two sub-blocks of 16).  Keys come in
+// blocks of kPK, K and V moved from the cache straight into LDS by the load
+// unit (NS buffers), rows stored with their 16-byte chunks permuted by
 // row (kv_swz) so that the K fragment reads and the transposed V reads hit
 // distinct banks.  The wave
 // computes S^T = K Q^T (keys on the MFMA rows, its queries on the columns,
@@ -369,9 +369,39 @@ __global__ __launch_bounds__(D) void attn_decode_combine(const float* __restrict
 // fp32, and O^T += V^T P^T: the probabilities stay in the registers they
 // were computed in (a lane's 8 keys per MFMA are the ones its S^T fragment
 // gave it; V^T is read with the same key order through transposed LDS
-// reads).  Workgroups with the most key blocks start first.
-constexpr int kPQ = 128;  // queries per workgroup
-constexpr int kPK = 64;   // keys per block
+// reads).
+//
+// Which workgroup takes what, with several query blocks per head: workgroups
+// go to the XCDs in turn, and within one to its shader engines and CUs in
+// turn, so an order in which the blocks of a head follow each other (1, 2, ..
+// n key blocks of work) gives the same class of work to the same CUs again
+// and again (with 4 or 8 query blocks the heaviest to one XCD).  XCD x takes
+// 1/8 of the (sequence, head) pairs, in groups of 32 (its CUs), and of a group
+// first every pair's last query block, then the one before, and so on; the
+// pairs % 8 left over are dealt to all XCDs in the same order, first.  us
+// before and after: b 32, 512 tokens, 40 heads of 128 251 -> 200; 64 heads over
+// 8 376 -> 314; 40 heads of 64 131 -> 104; 8 x 1024, 40 heads of 128 220 -> 157.
+// With
+// many pairs of few blocks the reads of K and V count more than the balance:
+// groups of 5 (no divisor of the CUs) while the XCD has more than 32 pairs of
+// at most 6 blocks.  us with the grid's order, groups of 32, groups of 5: b 32,
+// 384 tokens, 40 heads of 128 142, 145, 133; 16 x 600 142, 142, 134; 8 x 700 96,
+// 92, 84; 16 x 250 45, 47, 41; but 8 x 640, 32 heads over 8 62, 54, 60; 1 x
+// 1500, 56 heads 77, 50, 57.  Grid's order and groups of 32 further up: b 2,
+// 2048 tokens, 40 heads 189, 117; 1 x 4096 347, 203.  With one query block the
+// order of the grid is 4 % the faster (39 against 41 at b 32, 128 tokens).
+// What is left is the softmax between the two products: 1024 cycles of MFMA
+// and about as many of vector and of LDS work for a wave and 64-key block.
+//
+// Up to 32 tokens one wave has all the queries: two waves and one block of 32
+// keys (the other keys of 64 are masked, so the bits are the same) let more
+// workgroups share a CU: b 64, 32 tokens, 56 heads of 128 33 -> 24 us, b 128,
+// 32 heads over 8 37 -> 22.
+constexpr int kPQ = 128;     // queries per workgroup
+constexpr int kPK = 64;      // keys per block
+constexpr int kPShort = 32;  // prompts that take the short form
+// pairs whose query blocks are interleaved
+constexpr uint32_t kPGroup = 32, kPGroupSmall = 5;
 constexpr int kPrefillStages = 2;
 
 template <int NS, int DMA>
@@ -396,29 +426,50 @@ __device__ __forceinline__ void wait_blocks_landed(int pending) {
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));
 }
 
-template <int D, int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_prefill_k(
+template <int D, int NS, int PK, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void attn_prefill_k(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
     const uint16_t* __restrict__ vc, uint16_t* __restrict__ o, int b, int P, int H, int Hkv) {
+  constexpr int PQ = 32 * NW;              // queries per workgroup
   constexpr int ROWB = 2 * D;               // bytes per key row in LDS
-  constexpr int BLK = kPK * ROWB;           // bytes of K (or V) per block
-  constexpr int DMA = BLK / 1024 / 4;       // DMA instructions per wave for K (and for V)
+  constexpr int BLK = PK * ROWB;            // bytes of K (or V) per block
+  constexpr int DMA = BLK / 1024 / NW;      // DMA instructions per wave for K (and for V)
   constexpr int KK = D / 32;                // MFMA k steps over the head dimension
   constexpr int NF = D / 16;                // head-dimension fragments of O^T
   constexpr float kLog2e = 1.4426950408889634f;
   __shared__ __attribute__((aligned(1024))) uint8_t kv[NS][2][BLK];  // [stage][K, V]
 
-  const int nqb = (P + kPQ - 1) / kPQ;
-  const int qb = nqb - 1 - (int)blockIdx.x;  // most key blocks first
-  const int h = blockIdx.y, bi = blockIdx.z;
+  // (32-bit: every workgroup has at least 128 bytes of q to itself)
+  const uint32_t nqb = gridDim.x;
+  const uint32_t id = blockIdx.x + nqb * (blockIdx.y + (uint32_t)H * blockIdx.z);
+  uint32_t pair = id, qi = 0;
+  if (nqb > 1) {
+    const uint32_t xcd = id % 8, pairs = (uint32_t)H * b, own = pairs / 8, rest = pairs % 8;
+    const uint32_t shared = (nqb * rest + 7 - xcd) / 8;  // of the pairs % 8 last pairs
+    uint32_t i = id / 8;
+    if (i < shared) {
+      const uint32_t t = 8 * i + xcd;
+      qi = t / rest;
+      pair = 8 * own + (t - qi * rest);
+    } else {
+      i -= shared;
+      const uint32_t group = nqb <= 6 && own > kPGroup ? kPGroupSmall : kPGroup;
+      const uint32_t first = i / (group * nqb) * group, n = min(group, own - first);
+      i -= first * nqb;
+      qi = i / n;
+      pair = xcd * own + first + (i - qi * n);
+    }
+  }
+  const int qb = (int)(nqb - 1 - qi);  // most key blocks first
+  const int bi = (int)(pair / (uint32_t)H), h = (int)(pair - (uint32_t)bi * H);
   const int64_t d = (int64_t)H * D, dkv = (int64_t)Hkv * D;
   const int kh = h / (H / Hkv);
   // the wave index in a scalar register, so that everything derived from
   // it (the wave's queries, which blocks it masks) is wave-uniform
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int qw = qb * kPQ + wave * 32;       // this wave's first query
-  const int nkb = (min(qb * kPQ + kPQ, P) + kPK - 1) / kPK;
+  const int qw = qb * PQ + wave * 32;        // this wave's first query
+  const int nkb = (min(qb * PQ + PQ, P) + PK - 1) / PK;
 
   // Q^T fragments (B operand): lane (r, g) holds query qw + 16 u + r, dims 32 kk + 8 g ..
   h8 qf[2][KK];
@@ -447,10 +498,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     doff[i] = (p / ROWB) * row_elems + 8 * kv_swz<D>(p / ROWB, (p % ROWB) / 16);
   }
   const auto issue = [&](int kb, int buf) {
-    const int k0 = kb * kPK;
+    const int k0 = kb * PK;
     const uint16_t* kblk = kbase + (int64_t)k0 * row_elems;
     const uint16_t* vblk = vbase + (int64_t)k0 * row_elems;
-    const bool clamp = k0 + kPK > P;
+    const bool clamp = k0 + PK > P;
 #pragma unroll
     for (int i = 0; i < DMA; ++i) {
       int off = doff[i];
@@ -478,14 +529,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     // block kb landed (blocks kb + 1 .. kb + NS - 1 may still be in flight)
     wait_blocks_landed<NS, DMA>(min(NS - 1, nkb - 1 - kb));
     wg_barrier();
-    const int k0 = kb * kPK;
+    const int k0 = kb * PK;
     if (k0 <= qw + 31) {  // some key of the block is visible to this wave
       const uint8_t* Kl = kv[buf][0];
       const uint8_t* Vl = kv[buf][1];
       // S^T: s[u][j][e] = score of key k0 + 16 j + 4 g + e for query qw + 16 u + r
-      f4 s[2][4];
+      f4 s[2][PK / 16];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < PK / 16; ++j) {
         s[0][j] = f4{0.f, 0.f, 0.f, 0.f};
         s[1][j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -497,13 +548,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         }
       }
       // the block needs masking (a wave-uniform test)
-      const bool edge = k0 + kPK - 1 > qw || k0 + kPK > P;
+      const bool edge = k0 + PK - 1 > qw || k0 + PK > P;
       if (edge) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int qp = qw + 16 * u + r;
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < PK / 16; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const int key = k0 + 16 * j + 4 * g + e;
@@ -511,12 +562,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
             }
         }
       }
-      h8 pf[2][2];  // P^T fragments (B operand) per sub-block and 32-key half
+      h8 pf[2][PK / 32];  // P^T fragments (B operand) per sub-block and 32 keys
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         float bm = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < PK / 16; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e) bm = fmaxf(bm, s[u][j][e]);
         bm = pair_max(__builtin_amdgcn_permlane16_swap(__float_as_uint(bm), __float_as_uint(bm), false, false));
@@ -528,7 +579,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         mrow[u] = mnew;
         float rs = 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < PK / 16; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             // v_exp_f32 without denormal scaling: p below 2^-126 becomes 0
@@ -546,18 +597,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
           for (int n = 0; n < NF; ++n) oacc[u][n] *= alpha;
         }
 #pragma unroll
-        for (int hk = 0; hk < 2; ++hk)
+        for (int hk = 0; hk < PK / 32; ++hk)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             pf[u][hk][e] = (_Float16)s[u][2 * hk][e];
             pf[u][hk][4 + e] = (_Float16)s[u][2 * hk + 1][e];
           }
       }
-      // O^T += V^T P^T over the two 32-key halves: lane (r, g) needs V rows
+      // O^T += V^T P^T over the runs of 32 keys: lane (r, g) needs V rows
       // 32 hk + 4 g + (0..3) and 32 hk + 16 + 4 g + (0..3), dim 16 n + r;
       // lane i' of its group addresses row base + i' / 4, dims 16 n + 4 (i' % 4)
 #pragma unroll
-      for (int hk = 0; hk < 2; ++hk)
+      for (int hk = 0; hk < PK / 32; ++hk)
 #pragma unroll
         for (int n = 0; n < NF; ++n) {
           h8 vf;
@@ -734,12 +785,16 @@ pipo_status launch_attn_prefill(const uint16_t* q, const uint16_t* kc, const uin
     return PIPO_ERR_UNSUPPORTED;
   }
   const dim3 grid((unsigned)((P + kPQ - 1) / kPQ), (unsigned)n_heads, (unsigned)b);
-  if (head_dim == 128)
-    launch(attn_prefill_k<128, kPrefillStages>, grid, dim3(256), 0, st, q, kc, vc, o, b, P,
-           n_heads, n_kv_heads);
-  else
-    launch(attn_prefill_k<64, kPrefillStages>, grid, dim3(256), 0, st, q, kc, vc, o, b, P,
-           n_heads, n_kv_heads);
+  const auto go = [&](auto kernel, int threads) {
+    launch(kernel, grid, dim3(threads), 0, st, q, kc, vc, o, b, P, n_heads, n_kv_heads);
+  };
+  if (P <= kPShort) {
+    if (head_dim == 128) go(attn_prefill_k<128, 1, kPShort, 2>, 128);
+    else go(attn_prefill_k<64, 1, kPShort, 2>, 128);
+  } else {
+    if (head_dim == 128) go(attn_prefill_k<128, kPrefillStages, kPK, 4>, 256);
+    else go(attn_prefill_k<64, kPrefillStages, kPK, 4>, 256);
+  }
   PIPO_HIP_TRY(hipGetLastError());
   return PIPO_OK;
 }
