@@ -11,9 +11,12 @@
 // the rows, heads on the columns, so a lane holds scores of one head), an
 // online softmax per head in fp32, and O^T += V^T P^T with V^T read by
 // transposed LDS reads in the key order that S^T left P in.  P goes to the
-// product as the sum of two fp16 values, hi = fp16(p) and lo = fp16(p - hi),
-// which keeps 22 of its bits.  Waves are merged in order through LDS, splits
-// by attn_decode_combine.
+// product in two fp16 parts of y = 2^15 p: hi = fp16(y) and lo = fp16(2^11 (y
+// - hi)), each with a sum of its own, put together as hi + 2^-11 lo at the
+// end.  That keeps 22 bits of every p down to 2^-29 of the largest one so far
+// (20 below its score) and 11, those of the output, down to 2^-40; what it
+// drops of smaller ones is under 2^-51 each.  Waves are merged in order
+// through LDS, splits by attn_decode_combine.
 //
 // Bound by HBM and the fixed cost of a launch.  The kernel it replaced did
 // the G dot products and accumulator updates on the vector units, about 150
@@ -27,6 +30,7 @@
 namespace pipo {
 
 constexpr int kGqaKeys = 32;  // keys of a block
+constexpr float kPScale = 32768.f, kLoScale = 2048.f;  // of P's two parts
 
 // Eight waves (128 KiB of LDS at head_dim 128, one workgroup per CU) while
 // that gives every workgroup a CU, else four, two workgroups per CU, so that
@@ -122,9 +126,9 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
     }
   };
 
-  f4 oacc[NF];
+  f4 ohi[NF], olo[NF];
 #pragma unroll
-  for (int n = 0; n < NF; ++n) oacc[n] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int n = 0; n < NF; ++n) ohi[n] = olo[n] = f4{0.f, 0.f, 0.f, 0.f};
   float mrow = -INFINITY, lrow = 0.f;
   Codes ck, cv;
   if constexpr (KV4) {
@@ -182,15 +186,25 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
       for (int e = 0; e < 4; ++e) {
         const float x = __builtin_amdgcn_exp2f((s[j][e] - mnew) * kLog2e);
         rs += x;
-        hi[4 * j + e] = (_Float16)x;
-        lo[4 * j + e] = (_Float16)(x - (float)hi[4 * j + e]);
+        s[j][e] = x;
+        // (fused, so that it is one instruction with the rounding)
+        hi[4 * j + e] = (_Float16)__builtin_fmaf(x, kPScale, 0.f);
       }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        lo[4 * j + e] = (_Float16)__builtin_fmaf(s[j][e], kPScale * kLoScale,
+                                                 (float)hi[4 * j + e] * -kLoScale);
     rs = pair_sum(__builtin_amdgcn_permlane16_swap(__float_as_uint(rs), __float_as_uint(rs), false, false));
     rs = pair_sum(__builtin_amdgcn_permlane32_swap(__float_as_uint(rs), __float_as_uint(rs), false, false));
     lrow = lrow * alpha + rs;
     if (__any(alpha != 1.f)) {  // the running maxima rarely grow after the first blocks
 #pragma unroll
-      for (int n = 0; n < NF; ++n) oacc[n] *= alpha;
+      for (int n = 0; n < NF; ++n) {
+        ohi[n] *= alpha;
+        olo[n] *= alpha;
+      }
     }
     if constexpr (!KV4 && DIRECT) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));  // V landed
     __builtin_amdgcn_sched_barrier(0);
@@ -204,15 +218,16 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
 #pragma unroll
         for (int e = 0; e < 4; ++e) vf[4 * half + e] = x[e];
       }
-      oacc[n] = mfma16(vf, hi, oacc[n]);
-      oacc[n] = mfma16(vf, lo, oacc[n]);
+      ohi[n] = mfma16(vf, hi, ohi[n]);
+      olo[n] = mfma16(vf, lo, olo[n]);
     }
     // this block's LDS is read
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // merge the waves: oacc[n][e] is dim 16 n + 4 g + e of head r
+  // merge the waves: element e of ohi[n] and olo[n] is dim 16 n + 4 g + e of
+  // head r
   float* const wacc = reinterpret_cast<float*>(lds + wave * (2 * BLK));  // [G][D]
   if (r < G) {
     if (g == 0) {
@@ -220,7 +235,12 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
       wl[wave][r] = lrow;
     }
 #pragma unroll
-    for (int n = 0; n < NF; ++n) *reinterpret_cast<f4*>(wacc + r * D + 16 * n + 4 * g) = oacc[n];
+    for (int n = 0; n < NF; ++n) {
+      f4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(olo[n][e], 1.f / kLoScale, ohi[n][e]);
+      *reinterpret_cast<f4*>(wacc + r * D + 16 * n + 4 * g) = v;
+    }
   }
   __syncthreads();
   for (int c = tid; c < G * D; c += W * 64) {
@@ -235,6 +255,7 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
       L += wl[w][j] * a;
       A += reinterpret_cast<const float*>(lds + w * (2 * BLK))[c] * a;
     }
+    A *= 1.f / kPScale;
     if (S == 1) {
       o[(int64_t)bi * d + (int64_t)h * D + cc] = f2h(A / L);
     } else {

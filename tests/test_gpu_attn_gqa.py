@@ -40,3 +40,39 @@ def test_attn_decode_gqa_edges(b, T, H, Hkv, D, scale, shift):
             want = gqa_attention(q[i:i + 1].astype(np.float64), kc[:, i].astype(np.float64),
                                  vc[:, i].astype(np.float64), H, Hkv)[0]
             assert np.abs(got[i] - want).max() <= 2e-3 * max(1.0, np.abs(want).max())
+
+
+def _run(q, kc, vc, H, Hkv, D, fmt=B.PIPO_KV_FP16, split=True):
+    """kc, vc: [T][b][...] rows as the cache holds them"""
+    T, b = kc.shape[:2]
+    dq, dk, dv, do = DB.from_array(q), DB.from_array(kc), DB.from_array(vc), DB(b * H * D * 2)
+    n = B.pipo_op_attn_decode_gqa_workspace_bytes(b, H, Hkv, D, T - 1) if split else 0
+    ws = DB(n) if n else None
+    B.pipo_op_attn_decode_gqa(dq.ptr, dk.ptr, dv.ptr, do.ptr, b, H, Hkv, D, T - 1, fmt,
+                              ws.ptr if ws else None, n)
+    B.pipo_dev_synchronize()
+    return do.to_array(np.float16, (b, H * D))
+
+
+@pytest.mark.parametrize("gap", [14, 17.5, 20, 23.5])
+@pytest.mark.parametrize("T,D,split", [(200, 64, False), (8192, 128, True), (8192, 128, False)])
+def test_attn_decode_gqa_small_probabilities(gap, T, D, split):
+    """A key of value 0 in every 32 and a long tail `gap` below its score, of
+    value 1000 or 50 000: the output is the tail's alone.  Tolerance: an fp16
+    output (2^-11) and what 22 bits of each probability and the fp32 exp2 of
+    an argument of 35 (2^-19 from rounding it) leave, twice over."""
+    print(f"gqa tail gap={gap} T={T} D={D} split={split}", flush=True)
+    H, Hkv = 8, 2
+    q = np.zeros((1, H * D), np.float16)
+    q[:, ::D] = 1
+    kc = np.zeros((T, 1, Hkv * D), np.float16)
+    vc = np.zeros((T, 1, Hkv * D), np.float16)
+    vc[:] = 1000 if gap < 20 else 50000
+    kc[:, :, ::D] = -gap
+    kc[::32, :, ::D] = 0
+    vc[::32] = 0
+    got = _run(q, kc, vc, H, Hkv, D, split=split).astype(np.float64)
+    want = gqa_attention(q.astype(np.float64), kc[:, 0].astype(np.float64),
+                         vc[:, 0].astype(np.float64), H, Hkv)
+    assert want.min() > 2.0 ** -14  # (a normal fp16 number)
+    assert np.abs(got / want - 1).max() <= 2.0 ** -11 + 2 * (2.0 ** -22 + 2.0 ** -19)
