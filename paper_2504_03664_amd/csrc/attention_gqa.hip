@@ -31,6 +31,7 @@ namespace pipo {
 
 constexpr int kGqaKeys = 32;  // keys of a block
 constexpr float kPScale = 32768.f, kLoScale = 2048.f;  // of P's two parts
+constexpr _Float16 kPMin = 5.9604644775390625e-8f16;    // 2^-24, the smallest fp16
 
 // Eight waves (128 KiB of LDS at head_dim 128, one workgroup per CU) while
 // that gives every workgroup a CU, else four, two workgroups per CU, so that
@@ -190,6 +191,9 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
         // (fused, so that it is one instruction with the rounding)
         hi[4 * j + e] = (_Float16)__builtin_fmaf(x, kPScale, 0.f);
       }
+    // never zero (lo takes it off again), so that an infinity in V comes out as
+    // one: under keys past the share, which repeat its last, and tiny p
+    hi = __builtin_elementwise_max(hi, h8(kPMin));
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -227,7 +231,8 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
   }
 
   // merge the waves: element e of ohi[n] and olo[n] is dim 16 n + 4 g + e of
-  // head r
+  // head r.  An infinity in V may make the low parts' sum NaN (some are zero
+  // or negative); the high parts' sum is the result then.
   float* const wacc = reinterpret_cast<float*>(lds + wave * (2 * BLK));  // [G][D]
   if (r < G) {
     if (g == 0) {
@@ -238,7 +243,10 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
     for (int n = 0; n < NF; ++n) {
       f4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(olo[n][e], 1.f / kLoScale, ohi[n][e]);
+      for (int e = 0; e < 4; ++e) {
+        const float sum = __builtin_fmaf(olo[n][e], 1.f / kLoScale, ohi[n][e]);
+        v[e] = sum == sum ? sum : ohi[n][e];
+      }
       *reinterpret_cast<f4*>(wacc + r * D + 16 * n + 4 * g) = v;
     }
   }

@@ -76,3 +76,33 @@ def test_attn_decode_gqa_small_probabilities(gap, T, D, split):
                          vc[:, 0].astype(np.float64), H, Hkv)
     assert want.min() > 2.0 ** -14  # (a normal fp16 number)
     assert np.abs(got / want - 1).max() <= 2.0 ** -11 + 2 * (2.0 ** -22 + 2.0 ** -19)
+
+
+@pytest.mark.parametrize("T,split", [(5, False), (70, False), (600, True), (600, False)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_attn_decode_gqa_infinite_values(T, D, split):
+    """An infinite value gives its sign in its own dimension and nothing else:
+    for the last key (repeated past the end of a block), for one in the middle
+    and for one whose score is 30 below the others; opposite infinities give
+    NaN.  The other dimensions keep their bits."""
+    print(f"gqa infinite values T={T} D={D} split={split}", flush=True)
+    H, Hkv = 8, 2
+    rng = np.random.default_rng(T + D)
+    q = (rng.standard_normal((1, H * D)) * 0.3).astype(np.float16)
+    kc = rng.standard_normal((T, 1, Hkv * D)).astype(np.float16)
+    vc = rng.standard_normal((T, 1, Hkv * D)).astype(np.float16)
+    q[:, ::D] = 1
+    low = T // 2 + 1
+    kc[low, :, ::D] = -30
+    plain = _run(q, kc, vc, H, Hkv, D, split=split)
+    inf = vc.copy()
+    inf[T - 1, 0, 3::D] = np.inf
+    inf[T // 2, 0, 20::D] = -np.inf
+    inf[low, 0, 37::D] = np.inf
+    inf[0, 0, 41::D], inf[T - 1, 0, 41::D] = np.inf, -np.inf
+    got = _run(q, kc, inf, H, Hkv, D, split=split).reshape(H, D)
+    assert (got[:, 3] == np.inf).all() and (got[:, 20] == -np.inf).all()
+    assert (got[:, 37] == np.inf).all() and np.isnan(got[:, 41]).all()
+    keep = [i for i in range(D) if i not in (3, 20, 37, 41)]
+    assert np.array_equal(got[:, keep].view(np.uint16),
+                          plain.reshape(H, D)[:, keep].view(np.uint16))
