@@ -2,9 +2,9 @@
 // (sequence, head) against keys 0..t, the G query heads of a key/value head
 // as columns of 16 x 16 products.
 //
-// A workgroup is W waves on one (sequence, key/value head, split); each wave
-// takes a contiguous share of the split's keys, 32 at a time, through LDS of
-// its own (no barrier in the key loop).  fp16 rows come straight from the
+// A workgroup is W waves on one (sequence, key/value head, split) that take
+// the split's keys by turns, 32 at a time, through LDS of their own (no
+// barrier in the key loop).  fp16 rows come straight from the
 // cache by the load unit, INT4 rows through registers, where they are
 // expanded; both are laid out as in attn_prefill_k (kv_swz), so the two cache
 // formats run the same arithmetic.  The wave computes S^T = K Q^T (keys on
@@ -36,13 +36,18 @@ constexpr _Float16 kPMin = 5.9604644775390625e-8f16;    // 2^-24, the smallest f
 // Eight waves (128 KiB of LDS at head_dim 128, one workgroup per CU) while
 // that gives every workgroup a CU, else four, two workgroups per CU, so that
 // one's loads run beside the other's products (b 64, 8 key/value heads, 544
-// keys: 32.9 us with eight, 30.8 with four; b 16: 9.9 and 11.9).
-constexpr int kGqaWideWGs = 256;
+// keys: 32.9 us with eight, 30.8 with four; b 16: 9.9 and 11.9).  Above two
+// workgroups per CU, one or two waves where there are no more blocks: idle
+// waves hold LDS that other workgroups need (b 256, 32/8 heads, 9 keys: 14.8
+// us with four, 6.9 with one; 64 keys: 21.7 and 16.3 with two).
+constexpr int kGqaWideWGs = kAttnGqaWGs;
 
-// DIRECT: fp16 rows by global -> LDS loads (16-byte aligned cache), else
-// through registers
+// DIRECT: fp16 rows by global -> LDS loads (16-byte aligned cache); INT4 rows
+// and others through registers.  Two waves per SIMD are what LDS leaves room for; told
+// so, the compiler keeps the sums in plain registers (those of four waves
+// went to accumulation registers, with 400 moves between the two).
 template <int D, int W, bool KV4, bool DIRECT>
-__global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
+__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2))) void attn_decode_gqa_k(
     const uint16_t* __restrict__ q, const void* __restrict__ kc, const void* __restrict__ vc,
     uint16_t* __restrict__ o, float* __restrict__ part, int b, int Hkv, int G, int t, int chunk) {
   constexpr int ROWB = 2 * D, BLK = kGqaKeys * ROWB;  // bytes of a key row, of K (or V) per block
@@ -57,10 +62,10 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
   const int r = lane & 15, g = lane >> 4;
   const int H = Hkv * G, T = t + 1;
   const int64_t d = (int64_t)H * D, dkv = (int64_t)Hkv * D;
-  // this wave's keys [p0, p1): the split's keys in W contiguous shares
-  const int s0 = sp * chunk, s1 = min(T, s0 + chunk);
-  const int share = (s1 - s0 + W - 1) / W;
-  const int p0 = s0 + wave * share, p1 = min(s1, p0 + share);
+  // the split's keys end at p1, and this wave takes every W-th block of them
+  // from p0 on: all workgroups then read the same range of positions at a time
+  // (contiguous shares touch W times the pages; b 128, 2048 keys 190 -> 184 us)
+  const int p1 = min(T, (sp + 1) * chunk), p0 = sp * chunk + wave * kGqaKeys;
   uint8_t* const kl = lds + wave * (2 * BLK);
   uint8_t* const vl = kl + BLK;
 
@@ -77,53 +82,58 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
   const char* const kbase = static_cast<const char*>(kc) + (int64_t)bi * row_bytes;
   const char* const vbase = static_cast<const char*>(vc) + (int64_t)bi * row_bytes;
 
-  // fp16: block at position p into LDS, rows past the share repeat its last
+  // fp16: the 16 bytes of load i of the block at position p; rows past the
+  // split repeat its last
   const int drow = lane / (ROWB / 16);
+  const auto source = [&](const char* base, int p, int i) {
+    const int row = i * RPD + drow;
+    const int c = kv_swz<D>(row, lane % (ROWB / 16));
+    return base + (int64_t)min(p + row, p1 - 1) * pos_bytes + (int64_t)kh * ROWB + 16 * c;
+  };
+  // (read once per step, so non-temporal: b 128, 32/8 heads, 2048 keys 184 ->
+  // 170 us, 6.3 TB/s)
   const auto issue = [&](const char* base, uint8_t* dst, int p) {
-    h8 x[DIRECT ? 1 : DMA];
 #pragma unroll
-    for (int i = 0; i < DMA; ++i) {
-      const int row = i * RPD + drow;
-      const int c = kv_swz<D>(row, lane % (ROWB / 16));
-      const char* src =
-          base + (int64_t)min(p + row, p1 - 1) * pos_bytes + (int64_t)kh * ROWB + 16 * c;
-      if constexpr (DIRECT)
-        lds_dma16(src, dst + i * 1024);
-      else
-        x[i] = load_h8(reinterpret_cast<const uint16_t*>(src));
-    }
-    if constexpr (!DIRECT) {
-#pragma unroll
-      for (int i = 0; i < DMA; ++i) *reinterpret_cast<h8*>(dst + i * 1024 + lane * 16) = x[i];
-    }
+    for (int i = 0; i < DMA; ++i) lds_dma16_w<true>(source(base, p, i), dst + i * 1024);
   };
-  // INT4: 32 elements (one 16-byte word of codes, one pair) per lane and pass
+  // through registers: INT4, 32 elements (one 16-byte word of codes, one
+  // pair) per lane and pass, or fp16 as `issue` moves it
   constexpr int LPR = D / 32, PASS = kGqaKeys * LPR / 64;  // lanes per row, passes
-  struct Codes {
-    u32x4 c[PASS];
-    uint32_t sm[PASS];
+  constexpr int WORDS = KV4 ? PASS : DMA;
+  struct Block {
+    u32x4 c[WORDS];
+    uint32_t sm[WORDS];
   };
-  const auto load4 = [&](const char* base, int p) {
-    Codes x;
+  const auto load = [&](const char* base, int p) {
+    Block x;
 #pragma unroll
-    for (int i = 0; i < PASS; ++i) {
-      const int row = i * (64 / LPR) + lane / LPR, e = 32 * (lane % LPR);
-      const char* src = base + (int64_t)min(p + row, p1 - 1) * pos_bytes;
-      x.c[i] = *reinterpret_cast<const u32x4*>(src + ((int64_t)kh * D + e) / 2);
-      x.sm[i] = *reinterpret_cast<const uint32_t*>(src + dkv / 2 + ((int64_t)kh * D + e) / 64 * 4);
+    for (int i = 0; i < WORDS; ++i) {
+      if constexpr (KV4) {
+        const int row = i * (64 / LPR) + lane / LPR, e = 32 * (lane % LPR);
+        const char* src = base + (int64_t)min(p + row, p1 - 1) * pos_bytes;
+        x.c[i] = *reinterpret_cast<const u32x4*>(src + ((int64_t)kh * D + e) / 2);
+        x.sm[i] =
+            *reinterpret_cast<const uint32_t*>(src + dkv / 2 + ((int64_t)kh * D + e) / 64 * 4);
+      } else {
+        x.c[i] = load_u32x4_stream(source(base, p, i));
+      }
     }
     return x;
   };
-  const auto expand4 = [&](const Codes& x, uint8_t* dst) {
+  const auto store = [&](const Block& x, uint8_t* dst) {
 #pragma unroll
-    for (int i = 0; i < PASS; ++i) {
-      const int row = i * (64 / LPR) + lane / LPR;
-      h2 s2, m2;
-      scale_min_pairs(x.sm[i], s2, m2);
+    for (int i = 0; i < WORDS; ++i) {
+      if constexpr (KV4) {
+        const int row = i * (64 / LPR) + lane / LPR;
+        h2 s2, m2;
+        scale_min_pairs(x.sm[i], s2, m2);
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
-        *reinterpret_cast<h8*>(dst + row * ROWB + 16 * kv_swz<D>(row, 4 * (lane % LPR) + w)) =
-            dequant8_fp8(x.c[i][w], s2, m2);
+        for (int w = 0; w < 4; ++w)
+          *reinterpret_cast<h8*>(dst + row * ROWB + 16 * kv_swz<D>(row, 4 * (lane % LPR) + w)) =
+              dequant8_fp8(x.c[i][w], s2, m2);
+      } else {
+        *reinterpret_cast<u32x4*>(dst + i * 1024 + lane * 16) = x.c[i];
+      }
     }
   };
 
@@ -131,27 +141,26 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
 #pragma unroll
   for (int n = 0; n < NF; ++n) ohi[n] = olo[n] = f4{0.f, 0.f, 0.f, 0.f};
   float mrow = -INFINITY, lrow = 0.f;
-  Codes ck, cv;
-  if constexpr (KV4) {
+  Block ck, cv;
+  if constexpr (!DIRECT) {
     if (p0 < p1) {
-      ck = load4(kbase, p0);
-      cv = load4(vbase, p0);
+      ck = load(kbase, p0);
+      cv = load(vbase, p0);
     }
   }
-  for (int p = p0; p < p1; p += kGqaKeys) {
-    if constexpr (KV4) {
-      expand4(ck, kl);
-      expand4(cv, vl);
-      if (p + kGqaKeys < p1) {  // the next block's codes travel beside this block's products
-        ck = load4(kbase, p + kGqaKeys);
-        cv = load4(vbase, p + kGqaKeys);
-      }
-      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
-    } else {
+  for (int p = p0; p < p1; p += W * kGqaKeys) {
+    if constexpr (DIRECT) {
       issue(kbase, kl, p);
       issue(vbase, vl, p);
-      __builtin_amdgcn_s_waitcnt(DIRECT ? waitcnt_imm(DMA, false)  // K landed
-                                        : waitcnt_imm(63, true));
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(DMA, false));  // K landed
+    } else {
+      store(ck, kl);
+      store(cv, vl);
+      if (p + W * kGqaKeys < p1) {  // the next block travels beside this block's products
+        ck = load(kbase, p + W * kGqaKeys);
+        cv = load(vbase, p + W * kGqaKeys);
+      }
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
     }
     __builtin_amdgcn_sched_barrier(0);
     // s[j][e]: score of key p + 16 j + 4 g + e for head r
@@ -192,7 +201,7 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
         hi[4 * j + e] = (_Float16)__builtin_fmaf(x, kPScale, 0.f);
       }
     // never zero (lo takes it off again), so that an infinity in V comes out as
-    // one: under keys past the share, which repeat its last, and tiny p
+    // one: under keys past the split, which repeat its last, and tiny p
     hi = __builtin_elementwise_max(hi, h8(kPMin));
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -210,7 +219,7 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
         olo[n] *= alpha;
       }
     }
-    if constexpr (!KV4 && DIRECT) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));  // V landed
+    if constexpr (DIRECT) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));  // V landed
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int n = 0; n < NF; ++n) {
@@ -258,7 +267,7 @@ __global__ __launch_bounds__(W * 64) void attn_decode_gqa_k(
     for (int w = 1; w < W; ++w) M = fmaxf(M, wm[w][j]);
     float L = 0.f, A = 0.f;
 #pragma unroll
-    for (int w = 0; w < W; ++w) {  // a share may be empty (its maximum -inf)
+    for (int w = 0; w < W; ++w) {  // a wave may have no key (its maximum -inf)
       const float a = __builtin_amdgcn_exp2f((wm[w][j] - M) * kLog2e);
       L += wl[w][j] * a;
       A += reinterpret_cast<const float*>(lds + w * (2 * BLK))[c] * a;
@@ -281,12 +290,18 @@ template <int D, bool KV4, bool DIRECT>
 static void launch_gqa_d(const uint16_t* q, const void* kc, const void* vc, uint16_t* o, int b,
                          int Hkv, int G, int t, int S, int chunk, float* part, hipStream_t st) {
   const dim3 grid((unsigned)Hkv, (unsigned)b, (unsigned)S);
-  if ((int64_t)b * Hkv * S <= kGqaWideWGs)
-    launch(attn_decode_gqa_k<D, 8, KV4, DIRECT>, grid, dim3(512), 0, st, q, kc, vc, o, part, b,
-           Hkv, G, t, chunk);
+  const int64_t wgs = (int64_t)b * Hkv * S;
+  const auto go = [&](auto kernel, int waves) {
+    launch(kernel, grid, dim3(waves * 64), 0, st, q, kc, vc, o, part, b, Hkv, G, t, chunk);
+  };
+  if (wgs <= kGqaWideWGs)
+    go(attn_decode_gqa_k<D, 8, KV4, DIRECT>, 8);
+  else if (wgs > 2 * kGqaWideWGs && chunk <= kGqaKeys)
+    go(attn_decode_gqa_k<D, 1, KV4, DIRECT>, 1);
+  else if (wgs > 2 * kGqaWideWGs && chunk <= 2 * kGqaKeys)
+    go(attn_decode_gqa_k<D, 2, KV4, DIRECT>, 2);
   else
-    launch(attn_decode_gqa_k<D, 4, KV4, DIRECT>, grid, dim3(256), 0, st, q, kc, vc, o, part, b,
-           Hkv, G, t, chunk);
+    go(attn_decode_gqa_k<D, 4, KV4, DIRECT>, 4);
 }
 
 void launch_decode_gqa(const uint16_t* q, const void* kc, const void* vc, uint16_t* o, int b,
@@ -295,10 +310,10 @@ void launch_decode_gqa(const uint16_t* q, const void* kc, const void* vc, uint16
   const bool direct = (reinterpret_cast<uintptr_t>(kc) | reinterpret_cast<uintptr_t>(vc)) % 16 == 0;
   const auto go = [&](auto kernel) { kernel(q, kc, vc, o, b, Hkv, G, t, S, chunk, part, st); };
   if (head_dim == 128)
-    go(kv4 ? launch_gqa_d<128, true, true>
+    go(kv4 ? launch_gqa_d<128, true, false>
            : (direct ? launch_gqa_d<128, false, true> : launch_gqa_d<128, false, false>));
   else
-    go(kv4 ? launch_gqa_d<64, true, true>
+    go(kv4 ? launch_gqa_d<64, true, false>
            : (direct ? launch_gqa_d<64, false, true> : launch_gqa_d<64, false, false>));
 }
 

@@ -179,5 +179,6 @@ constexpr int kAttnDecodeMaxT = 65536;
 constexpr int kAttnDecodeMaxSplits = 16;
 constexpr int kAttnDecodeMinWGs = 768;
 constexpr int kAttnDecodeWideWGs = 1536;
+constexpr int kAttnGqaWGs = 256;  // workgroups of grouped decode that have a CU each
 
 }  // namespace pipo

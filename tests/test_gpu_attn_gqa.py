@@ -5,7 +5,7 @@ the oracle's attention.  Tolerance: fp16 output (2^-11) and hardware exp2."""
 import numpy as np
 import pytest
 
-from oracle import gqa_attention
+from oracle import dequant_int4_g64, gqa_attention, quant_kv_int4_g64
 from paper_2504_03664_amd import binding as B
 from paper_2504_03664_amd.binding import DeviceBuffer as DB
 
@@ -106,3 +106,34 @@ def test_attn_decode_gqa_infinite_values(T, D, split):
     keep = [i for i in range(D) if i not in (3, 20, 37, 41)]
     assert np.array_equal(got[:, keep].view(np.uint16),
                           plain.reshape(H, D)[:, keep].view(np.uint16))
+
+
+@pytest.mark.parametrize("b,T,H,Hkv,D", [
+    (1, 1, 8, 4, 64), (1, 7, 8, 2, 128), (2, 33, 16, 4, 64), (1, 257, 8, 4, 128),  # eight waves
+    (65, 40, 16, 4, 64), (33, 130, 32, 8, 128), (33, 2050, 16, 8, 64),             # four
+    (65, 33, 32, 8, 128), (129, 64, 16, 4, 64), (130, 65, 8, 4, 128),              # two, four
+    (129, 7, 8, 4, 128), (129, 32, 16, 4, 64), (257, 1, 16, 4, 64)])               # one
+def test_attn_decode_gqa_waves_and_int4(b, T, H, Hkv, D):
+    """Every number of waves, with as many blocks and more, over fp16 rows
+    against the oracle (the first and last sequence) and over INT4 rows against
+    the fp16 kernel on the expanded rows, bit for bit."""
+    print(f"gqa waves b={b} T={T} H={H}/{Hkv} D={D}", flush=True)
+    rng = np.random.default_rng(T * 11 + b)
+    dkv = Hkv * D
+    q = (rng.standard_normal((b, H * D)) * 0.3).astype(np.float16)
+    rows = []
+    for _ in range(2):
+        codes, sm = quant_kv_int4_g64(rng.standard_normal((T * b, dkv)).astype(np.float16))
+        packed = np.concatenate([codes, np.ascontiguousarray(sm.reshape(T * b, -1)).view(np.uint8)],
+                                axis=1).reshape(T, b, -1)
+        rows.append((packed, dequant_int4_g64(codes, sm, np.float64).astype(np.float16)
+                     .reshape(T, b, dkv)))
+    (k4, kc), (v4, vc) = rows
+    for split in (True, False):
+        got = _run(q, kc, vc, H, Hkv, D, split=split)
+        for i in (0, b - 1):
+            want = gqa_attention(q[i:i + 1].astype(np.float64), kc[:, i].astype(np.float64),
+                                 vc[:, i].astype(np.float64), H, Hkv)[0]
+            assert np.abs(got[i] - want).max() <= 2e-3 * max(1.0, np.abs(want).max())
+        got4 = _run(q, k4, v4, H, Hkv, D, fmt=B.PIPO_KV_INT4_G64, split=split)
+        assert np.array_equal(got.view(np.uint16), got4.view(np.uint16))
