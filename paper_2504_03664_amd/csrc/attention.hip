@@ -668,8 +668,16 @@ int attn_decode_splits(int b, int n_heads, int n_kv_heads, int t, bool kv4) {
     // grouped: a workgroup's eight waves already share its keys, so splits
     // only where they fill the chip and keep 512 keys each, up to 8 (2048 each
     // beyond: merging more costs more than it gains; b 1, 8000 keys: 14.8 us
-    // with 8, 15.9 with 16)
-    const int fill = (int)std::max<int64_t>(1, 256 / ((int64_t)b * n_kv_heads));
+    // with 8, 15.9 with 16).  Between one workgroup per CU and one and a half the
+    // unsplit grid gives a few CUs two and leaves the others waiting for
+    // them: four splits (32/8 heads, us: b 33, 2048 keys 63 -> 55, 8000 keys
+    // 240 -> 187, b 48, 8000 keys 276 -> 248; but b 56, 448 workgroups, 2048
+    // keys 80.0 -> 81.4, and b 33, 544 keys, too few for a range, 19 -> 25).
+    // With ranges of 2000 keys they pay up to two and a half (b 64 342 -> 332,
+    // heads of 64 193 -> 180; b 80 430 -> 414; b 90 456 -> 482).
+    const int64_t wgs = (int64_t)b * n_kv_heads;
+    const bool even = wgs > kAttnGqaWGs && 2 * wgs <= (T >= 8000 ? 5 : 3) * kAttnGqaWGs;
+    const int fill = even ? 4 : (int)std::max<int64_t>(1, kAttnGqaWGs / wgs);
     const int keys = std::max(std::min(T / 512, 8), std::min(T / 2048, kAttnDecodeMaxSplits));
     const int S = std::max(1, std::min(fill, keys));
     const int chunk = (T + S - 1) / S;
