@@ -50,8 +50,8 @@ enum { PIPO_EPI_F16 = 0, PIPO_EPI_RELU_F16 = 1, PIPO_EPI_ADD_F32 = 2, PIPO_EPI_F
  * sums go to `workspace` (device, caller-owned, contents arbitrary) of
  * pipo_op_gemm_workspace_bytes(M, N, K, wfmt) bytes; a second kernel adds
  * them in a fixed order and applies the epilogue.  With less (or NULL)
- * workspace the GEMM takes as many of its K ranges as fit, or runs unsplit;
- * the result is the same up to rounding.  Calls sharing a workspace must not
+ * workspace the GEMM takes the tiles that run best with the K ranges that
+ * fit, or unsplit; the result is the same up to rounding.  Calls sharing a workspace must not
  * overlap in time.  For a given (M, N, K, wfmt, epilogue) and room in the
  * workspace the summation order is fixed, so repeated calls give the same
  * bits.

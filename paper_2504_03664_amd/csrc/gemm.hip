@@ -18,8 +18,8 @@
 //     128 x 64 fed by global -> LDS loads through rings of LDS stages; INT4
 //     codes reach LDS the same way and are expanded there, once per tile;
 //     fp16 may split K like gemm_slab.
-//   * gemm_tiled (M > 16, operands that are not 16-byte aligned): 128 x 128
-//     output tiles, K staged through registers into double-buffered LDS in
+//   * gemm_tiled (M > 16 and operands that are not 16-byte aligned, or fp16
+//     prefill with few big tiles that cannot be split): 128 x 128 output tiles, K staged through registers into double-buffered LDS in
 //     steps of 64, 4 waves of 64 x 64; tiles ordered per XCD so that each
 //     XCD's L2 serves a compact block.
 // The decode kernels read each weight once per pass and do so with
@@ -370,7 +370,8 @@ void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStrea
 }
 
 // ---------------------------------------------------------------------------
-// tiled GEMM (operands off 16-byte alignment)
+// tiled GEMM (operands off 16-byte alignment, and fp16 prefill with few big
+// tiles that cannot be split: see plan_prefill)
 constexpr int kTBM = 128, kTBN = 128, kTBK = 64, kTPad = 8;
 constexpr int kTThreads = 256;  // 2 x 2 waves of 64 x 64
 constexpr int kTGroupM = 4;
@@ -880,11 +881,12 @@ struct GemmPlan {
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// K ranges: the largest power of two up to the cap that keeps the grid within
-// kMaxWGs workgroups and every range at least kper_min long
-static int split_k(int64_t wgs, int64_t K, int64_t kper_min) {
+// K ranges: the largest power of two up to the cap (and the `fit` the workspace
+// holds) that keeps the grid within kMaxWGs workgroups and every range at
+// least kper_min long
+static int split_k(int64_t wgs, int64_t K, int64_t kper_min, int fit = kMaxSplits) {
   int S = 1;
-  while (S < kMaxSplits && wgs * 2 * S <= kMaxWGs && K % (2ll * S * 128) == 0 &&
+  while (2 * S <= fit && wgs * 2 * S <= kMaxWGs && K % (2ll * S * 128) == 0 &&
          K / (2 * S) >= kper_min)
     S *= 2;
   return S;
@@ -935,8 +937,11 @@ static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool
 // M <= 32 from 8192) take 96 columns (M = 64, 21504 x 7168: 62.5 -> 51.9); at
 // M <= 32 and N <= 8192 32 columns and no split measured best (8192 x 8192:
 // 29.3 -> 24.0).  Splitting K pays only for its second launch (about 2.5 us)
-// when a range is long enough: not below K = 1536.
-static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4) {
+// when a range is long enough: not below K = 1536.  Where the workspace does
+// not hold the ranges that wide workgroups need, the narrow ones take over
+// (4096 x 14336, one range: fp16 M = 32 82 -> 35, M = 64 97 -> 65, INT4 M = 128
+// 120 -> 79).
+static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, int fit) {
   const int mf = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
   GemmPlan p{kSlab};
   int cols;
@@ -963,7 +968,18 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4) {
     p.slab = mf == 4 ? (narrow ? kF16M64n64 : kF16M64n128) : (narrow ? kF16M128n64 : kF16M128n128);
     cols = narrow ? 64 : 128;
   }
-  if (K >= 1536) p.splits = split_k(ceil_div(N, cols), K, 256);
+  if (K < 1536) return p;
+  p.splits = split_k(ceil_div(N, cols), K, 256);
+  if (p.splits > fit) {
+    const int64_t narrow = ceil_div(N, !w4 && mf == 2 ? 32 : 64);
+    if (narrow <= kMaxWGs) {
+      p.slab = w4 ? (mf == 2 ? kW4M32n64 : (mf == 4 ? kW4M64n64 : kW4M128n64))
+                  : (mf == 2 ? kF16M32n32 : (mf == 4 ? kF16M64n64 : kF16M128n64));
+      p.splits = split_k(narrow, K, 256, fit);
+    } else {
+      p.splits = fit;
+    }
+  }
   return p;
 }
 
@@ -976,26 +992,48 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4) {
 // under 512 (four chunks a group) stays with one group.  fp16: big tiles with
 // K ranges (M = 512, 4096 x 14336: 202 -> 71; 28672 x 4096 202 -> 104), and
 // 128 x 128 slab tiles where even 8 ranges give few workgroups (M = 200,
-// 768 x 3072: 46 -> 15).  Outputs of fewer than 512 columns are no layer's
-// and stay unsplit.
-static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4) {
+// 768 x 3072: 46 -> 15).
+//
+// The ranges are those that fit the workspace.  Where the ones that a wide
+// tile needs do not, 128 x 128 slab tiles take its place while they are at
+// most kMaxWGs (4096 x 14336, one range: fp16 M = 509 254 -> 141, INT4 194 ->
+// 121; 128 x 128 tiles through registers, gemm_tiled, take 229 and 326);
+// fragment-ordered fp16 keeps the big ones if the ranges that fit give 80
+// workgroups (5120 x 20480, two ranges: M = 400, 80, 190 against 199; M = 768,
+// 120, 199 against 212).  Above kMaxWGs, fp16 big tiles that cannot be split and are half a chip or less
+// (M = 1500, 4096 x 14336: 251 against 270 with gemm_tiled) lose to gemm_tiled
+// where their start counts (K under 1024: M = 1500, 3072 x 768 21.5 against
+// 20.5) and where W is row-major, 64 bytes of a row per load (337 against 259).
+// Outputs of fewer than 512 columns stay unsplit: the workspace query answers
+// 0 for them, as callers that size their buffers by it have seen (M = 150,
+// 384 x 1536: 19 us where four ranges would take 11; 26 with gemm_tiled).
+static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4, bool packed, int fit) {
   const int64_t big = ceil_div(M, 256) * ceil_div(N, 256), mt = ceil_div(M, 128);
+  const int64_t t128 = mt * ceil_div(N, 128), t256 = mt * ceil_div(N, 256);
   const int64_t kper = N < 512 ? K : 512;
   if (w4) {
     if (big >= 192) return {kBig};
     if (K < 512) return {kSlab, kW4M128n256k1};
-    const int64_t t128 = mt * ceil_div(N, 128);
-    if (t128 <= kMaxWGs && K < 8192) return {kSlab, kW4M128n128, split_k(t128, K, kper)};
-    return {kSlab, kW4M128n256, split_k(mt * ceil_div(N, 256), K, kper)};
+    if (t128 <= kMaxWGs && (K < 8192 || split_k(t256, K, kper) > fit))
+      return {kSlab, kW4M128n128, split_k(t128, K, kper, fit)};
+    return {kSlab, kW4M128n256, split_k(t256, K, kper, fit)};
   }
   const int S = split_k(big, K, kper);
-  if (big * S <= 64) return {kSlab, kF16M128n128, split_k(mt * ceil_div(N, 128), K, kper)};
-  return {kBig, 0, S};
+  if (big * S > 64) {
+    const int s = S < fit ? S : fit;
+    if (s == S ? S > 1 || big > 128 : packed && s > 1 && big * s >= 80) return {kBig, 0, s};
+    if (t128 > kMaxWGs)
+      return big * s <= 128 && (!packed || K < 1024) ? GemmPlan{kTiled} : GemmPlan{kBig, 0, s};
+  }
+  return {kSlab, kF16M128n128, split_k(t128, K, kper, fit)};
 }
 
-static GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool packed) {
+// fit: the most K ranges the workspace has room for
+static GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool packed,
+                          int fit = kMaxSplits) {
   if (M <= kSkinnyMaxM) return plan_m16(M, N, K, w4, epi, packed);
-  return M <= kDecodeMaxM ? plan_decode(M, N, K, w4) : plan_prefill(M, N, K, w4);
+  return M <= kDecodeMaxM ? plan_decode(M, N, K, w4, fit)
+                          : plan_prefill(M, N, K, w4, packed, fit);
 }
 
 int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4) {
@@ -1044,11 +1082,9 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
     PIPO_HIP_TRY(hipGetLastError());
     return PIPO_OK;
   } else {
-    GemmPlan p = gemm_plan(a.M, a.N, a.K, W4, EPI, PK);
-    // as many of the planned K ranges as the workspace has room for
-    while (p.splits > 1 && (ws == nullptr || a.M * a.N >= ((int64_t)1 << 31) ||
-                            ws_bytes < (int64_t)p.splits * a.M * a.N * 4))
-      p.splits /= 2;
+    int fit = ws == nullptr || a.M * a.N >= ((int64_t)1 << 31) ? 1 : kMaxSplits;
+    while (fit > 1 && ws_bytes < (int64_t)fit * a.M * a.N * 4) fit /= 2;
+    GemmPlan p = gemm_plan(a.M, a.N, a.K, W4, EPI, PK, fit);
     // row-major INT4 at M <= 32: see gemm_stream_w4 (same K ranges)
     if (W4 && !PK && p.kernel == kSlab && p.slab == kW4M32n128) p.kernel = kStreamW4;
     // loads straight into LDS take 16 bytes at a time: operands off that

@@ -71,3 +71,37 @@ def test_gemm_unaligned_operands_exact(M, w4):
         B.pipo_op_gemm_f16(dX.ptr + 2, dW.ptr, None, dO.ptr, M, N, K, B.PIPO_EPI_F32)
     B.pipo_dev_synchronize()
     assert np.array_equal(dO.to_array(np.float32, (M, N)).astype(np.float64), want)
+
+
+# (M, N, K, w4): a workspace with room for part of the K ranges, where other
+# tiles take over: narrow ones in decode and where those would be too many;
+# 128 x 128 tiles, big tiles with fewer ranges or none, and gemm_tiled in prefill
+PARTIAL = [(20, 144, 16384, True), (20, 144, 16384, False), (32, 8320, 2048, False),
+           (40, 144, 16384, True), (64, 144, 16384, False), (70, 80, 16384, True),
+           (100, 144, 8448, False), (130, 8208, 1024, False), (130, 20496, 2048, False),
+           (130, 10256, 2048, False), (300, 12304, 1024, False), (300, 12304, 384, False),
+           (130, 528, 8192, True), (130, 528, 8192, False), (200, 1040, 1024, True)]
+
+
+@pytest.mark.parametrize("M,N,K,w4", PARTIAL)
+def test_gemm_partial_workspace_exact(M, N, K, w4):
+    """All of the workspace that the query asks for, a half, a quarter and one
+    byte less than that, and none."""
+    X, W, q, want = _case(M, N, K, w4)
+    full = B.pipo_op_gemm_workspace_bytes(M, N, K, B.PIPO_W_INT4_G64 if w4 else B.PIPO_W_FP16)
+    dX, dO, dWs = DB.from_array(X.astype(np.float16)), DB(M * N * 4), DB(max(full, 16))
+    for frag in (False, True):
+        if w4:
+            ops = [DB.from_array(x) for x in (B.pipo_pack_w4(*q) if frag else q)]
+            call = B.pipo_op_gemm_w4_frag if frag else B.pipo_op_gemm_w4
+        else:
+            W16 = W.astype(np.float16)
+            ops = [DB.from_array(B.pipo_pack_f16(W16) if frag else W16)]
+            call = B.pipo_op_gemm_f16_frag if frag else B.pipo_op_gemm_f16
+        for nbytes in sorted({full, full // 2, full // 4, max(full // 4 - 1, 0), 0}):
+            print(f"gemm workspace {nbytes} of {full} M={M} N={N} K={K} w4={w4} frag={frag}",
+                  flush=True)
+            call(dX.ptr, *[o.ptr for o in ops], None, dO.ptr, M, N, K, B.PIPO_EPI_F32,
+                 dWs.ptr if nbytes else None, nbytes)
+            B.pipo_dev_synchronize()
+            assert np.array_equal(dO.to_array(np.float32, (M, N)).astype(np.float64), want)
