@@ -202,7 +202,10 @@ typedef struct {
   int64_t chunk_bytes;       /* bytes per copy chunk (default 64 MiB; rounded to 4 KiB) */
   int32_t max_batch;         /* sequences per pass (>= 1) */
   int32_t max_seq;           /* prompt + generated positions per sequence (<= max_pos) */
-  int64_t hbm_budget_bytes;  /* 0: unlimited; else pipo_create fails with OOM_DEVICE above it */
+  int64_t hbm_budget_bytes;  /* 0: unlimited; else pipo_create fails with OOM_DEVICE above it.
+                                Without room for the prefill's GEMM workspace (at most 64 MiB)
+                                the context keeps the one of decode, and prefill runs slower
+                                and with another order of fp32 sums */
   int32_t debug_flags;       /* PIPO_DBG_* */
   int32_t copy_delay_us;     /* delay for PIPO_DBG_COPY_DELAY */
   int64_t pinned_budget_bytes; /* 0: pin host KV layers while the system grants pinned memory;

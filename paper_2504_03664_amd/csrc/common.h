@@ -117,10 +117,12 @@ struct GemmArgs {
 // M > 16 may split K over workgroups; their partial sums need `workspace`
 // (gemm_workspace_bytes; contents arbitrary, not shared by overlapping
 // launches).  With less the GEMM takes fewer K ranges, equal up to rounding.
-// gemm_workspace_bytes_upto covers the decode sizes (M <= 128) up to M_max.
+// gemm_workspace_bytes_upto covers every M up to M_max.  Up to kDecodeMaxM rows
+// are a decode step's.
 pipo_status launch_gemm(const GemmArgs& a, bool w4, int epi, float* workspace,
                         int64_t workspace_bytes, hipStream_t st);
 int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4);
+constexpr int64_t kDecodeMaxM = 128;
 int64_t gemm_workspace_bytes_upto(int64_t M_max, int64_t N, int64_t K, bool w4);
 pipo_status launch_layernorm(const float* x, const uint16_t* g, const uint16_t* b, uint16_t* y,
                              int64_t rows, int64_t d, int64_t src_stride, int64_t src_offset,

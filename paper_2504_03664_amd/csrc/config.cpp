@@ -224,16 +224,25 @@ HbmPlan hbm_plan(const pipo_shape& sh, const pipo_policy& pol) {
   p.argmax_ws = argmax_workspace_bytes(pol.max_batch, V);
   p.attn_ws = attn_decode_workspace_bytes(pol.max_batch, sh.n_heads, (int)(d / sh.n_heads),
                                           kAttnDecodeMaxSplits);
-  const int64_t shapes[5][3] = {
-      {qkv_rows(sh), d, w4}, {d, d, w4}, {fc1_rows(sh), d, w4}, {d, F, w4}, {V, d, 0}};
-  for (const auto& s : shapes)
-    p.gemm_ws = std::max(p.gemm_ws, gemm_workspace_bytes_upto(rows, s[0], s[1], s[2] != 0));
+  // GEMM K ranges: every row count of decode and prefill for the layer's
+  // matrices, max_batch rows for the head
+  const int64_t shapes[4][2] = {{qkv_rows(sh), d}, {d, d}, {fc1_rows(sh), d}, {d, F}};
+  const auto gemm_ws = [&](int64_t m_max) {
+    int64_t ws = gemm_workspace_bytes_upto(pol.max_batch, V, d, false);
+    for (const auto& s : shapes)
+      ws = std::max(ws, gemm_workspace_bytes_upto(m_max, s[0], s[1], w4));
+    return ws;
+  };
+  p.gemm_ws = gemm_ws(rows);
   const int64_t dkv = kv_width(sh);
   // INT4 cache: new rows are staged in fp16 (and rotated there) before quantization
   p.kstage = kv4 ? rows * dkv * 2 : 0;
   p.kv_row = kv4 ? dkv / 2 + dkv / 16 : 2 * dkv;
   p.kv_part = rows * p.kv_row;
   p.kv = (pol.kv_on_host ? pol.n_weight_slots : L) * 2 * p.kv_part;
+  // a budget that has no room for the prefill's ranges leaves those of decode
+  if (pol.hbm_budget_bytes > 0 && p.total() > pol.hbm_budget_bytes)
+    p.gemm_ws = gemm_ws(std::min(rows, kDecodeMaxM));
   return p;
 }
 
@@ -358,45 +367,51 @@ pipo_status pipo_configure(const pipo_shape* shape, int32_t wfmt, int32_t kv_fmt
   int64_t best_bytes = -1, best_slots = 0, need_hbm = -1, need_host = -1;
   int best_disk = 0;
   pipo_status first_err = PIPO_OK;
-  for (int w_host = 0; w_host <= 1; ++w_host)
-    for (int on_disk = 0; on_disk <= (w_host && disk > 0 ? 1 : 0); ++on_disk)
-      for (int e_host = 0; e_host <= 1; ++e_host)
-        for (int kv_host = 0; kv_host <= w_host; ++kv_host)
-          for (int slots : {3, 2, 1}) {
-            if (!w_host && !e_host && slots != 3) continue;  // nothing streams: slots unused
-            pipo_policy pol{};
-            pol.wfmt = wfmt;
-            pol.kv_fmt = kv_fmt;
-            pol.weights_on_host = w_host;
-            pol.weights_on_disk = on_disk;
-            pol.embed_on_host = e_host;
-            pol.kv_on_host = kv_host;
-            pol.n_weight_slots = slots;
-            pol.max_batch = max_batch;
-            pol.max_seq = max_seq;
-            const pipo_status st = normalize_policy(shape, &pol);
-            if (st != PIPO_OK) {
-              if (first_err == PIPO_OK) first_err = st;
-              continue;
+  // First with the prefill's whole GEMM workspace; where nothing fits, with as
+  // much as the budget leaves (hbm_plan).
+  for (const int64_t budget : {(int64_t)0, hbm}) {
+    if (best_bytes >= 0) break;
+    for (int w_host = 0; w_host <= 1; ++w_host)
+      for (int on_disk = 0; on_disk <= (w_host && disk > 0 ? 1 : 0); ++on_disk)
+        for (int e_host = 0; e_host <= 1; ++e_host)
+          for (int kv_host = 0; kv_host <= w_host; ++kv_host)
+            for (int slots : {3, 2, 1}) {
+              if (!w_host && !e_host && slots != 3) continue;  // nothing streams: slots unused
+              pipo_policy pol{};
+              pol.wfmt = wfmt;
+              pol.kv_fmt = kv_fmt;
+              pol.weights_on_host = w_host;
+              pol.weights_on_disk = on_disk;
+              pol.embed_on_host = e_host;
+              pol.kv_on_host = kv_host;
+              pol.n_weight_slots = slots;
+              pol.max_batch = max_batch;
+              pol.max_seq = max_seq;
+              const pipo_status st = normalize_policy(shape, &pol);
+              if (st != PIPO_OK) {
+                if (first_err == PIPO_OK) first_err = st;
+                continue;
+              }
+              pol.hbm_budget_bytes = budget;
+              const int64_t h = hbm_plan(*shape, pol).total();
+              const int64_t k = host_kv_bytes(*shape, pol) + host_weight_bytes(*shape, pol);
+              if (need_hbm < 0 || h < need_hbm) need_hbm = h;
+              if (h > hbm) continue;
+              if (need_host < 0 || k < need_host) need_host = k;  // among those that fit in HBM
+              if (k > host || disk_file_bytes(*shape, pol) > disk) continue;
+              const int64_t bytes = step_bytes(*shape, pol);
+              const bool better =
+                  best_bytes < 0 || bytes < best_bytes ||
+                  (bytes == best_bytes &&
+                   (on_disk < best_disk || (on_disk == best_disk && slots > best_slots)));
+              if (better) {
+                best = pol;
+                best_bytes = bytes;
+                best_slots = slots;
+                best_disk = on_disk;
+              }
             }
-            const int64_t h = hbm_plan(*shape, pol).total();
-            const int64_t k = host_kv_bytes(*shape, pol) + host_weight_bytes(*shape, pol);
-            if (need_hbm < 0 || h < need_hbm) need_hbm = h;
-            if (h > hbm) continue;
-            if (need_host < 0 || k < need_host) need_host = k;  // among those that fit in HBM
-            if (k > host || disk_file_bytes(*shape, pol) > disk) continue;
-            const int64_t bytes = step_bytes(*shape, pol);
-            const bool better =
-                best_bytes < 0 || bytes < best_bytes ||
-                (bytes == best_bytes &&
-                 (on_disk < best_disk || (on_disk == best_disk && slots > best_slots)));
-            if (better) {
-              best = pol;
-              best_bytes = bytes;
-              best_slots = slots;
-              best_disk = on_disk;
-            }
-          }
+  }
   if (best_bytes < 0) {
     if (first_err != PIPO_OK && need_hbm < 0) return first_err;
     if (need_host < 0) {

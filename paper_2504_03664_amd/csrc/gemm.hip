@@ -30,6 +30,8 @@
 // (M, N, K), the weight format and layout and the workspace, so a given call
 // always sums in the same order; no workgroup reads another workgroup's
 // results within a launch.
+#include <algorithm>
+
 #include "gemm_common.h"
 
 namespace pipo {
@@ -866,7 +868,7 @@ __global__ __launch_bounds__(kFThreads) void gemm_big_w4(GemmArgs a) {
 // cases the layout and alignment).  Times are us of one launch with its
 // merge over rotating weights (fragment order unless stated).
 // ---------------------------------------------------------------------------
-constexpr int64_t kSkinnyMaxM = 16, kDecodeMaxM = 128;
+constexpr int64_t kSkinnyMaxM = 16;
 constexpr int kMaxSplits = 8;
 // About one workgroup per CU measured best: a slab workgroup takes most of a
 // CU's LDS, so more of them only queue.
@@ -1042,15 +1044,16 @@ int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4) {
   return p.splits > 1 ? (int64_t)p.splits * M * N * 4 : 0;
 }
 
-// the decode sizes only: a prefill GEMM takes as many K ranges as fit in it
+// The plan is the same for every M of (16, 32], (32, 64], (64, 128] and of each
+// 128 rows beyond, and at most two ranges of kMaxWGs / 2 of the widest tiles
+// split: at most 64 MiB in all.
 int64_t gemm_workspace_bytes_upto(int64_t M_max, int64_t N, int64_t K, bool w4) {
   int64_t best = 0;
-  for (int64_t M : {(int64_t)32, (int64_t)64, kDecodeMaxM}) {
-    const int64_t m = M < M_max ? M : M_max;
-    const int64_t b = gemm_workspace_bytes(m, N, K, w4);
-    best = b > best ? b : best;
+  for (int64_t M = 32;; M += M < kDecodeMaxM ? M : 128) {
+    const int64_t m = std::min(M, M_max);
+    best = std::max(best, gemm_workspace_bytes(m, N, K, w4));
+    if (m == M_max || ceil_div(m, kBM) * ceil_div(N, kBN) > kMaxWGs / 2) return best;
   }
-  return best;
 }
 
 template <int NF, bool W4, int EPI, bool PK>

@@ -158,3 +158,35 @@ def test_configure_puts_the_layers_on_disk_only_when_host_memory_is_short():
     with pytest.raises(B.PipoError) as e:            # no room on disk either
         conf(16 * GB, 30 * GB)
     assert B.STATUS_NAMES[e.value.status] == "PIPO_ERR_OOM_HOST"
+
+
+def _gemm_ws(shape, wfmt, rows):
+    """Largest answer of the library's workspace query for a decoder layer's
+    matrices over every number of rows up to `rows`."""
+    d, F = shape.d_model, shape.d_ffn
+    return max(B.pipo_op_gemm_workspace_bytes(m, n, k, wfmt)
+               for n, k in ((3 * d, d), (d, d), (F, d), (d, F)) for m in range(1, rows + 1))
+
+
+@pytest.mark.parametrize("wfmt", ["fp16", "int4"])
+def test_plan_holds_every_prefill_gemm_workspace(wfmt):
+    """A context has the K ranges that the workspace query plans for every row
+    count of its prefill; a budget without room for them is still accepted as
+    long as those of decode (128 rows) fit, and is met."""
+    b, s, w = 1, 700, 0 if wfmt == "fp16" else 1
+    d, F = OPT30.d_model, OPT30.d_ffn
+    full, decode = _gemm_ws(OPT30, w, b * s), _gemm_ws(OPT30, w, 128)
+    assert decode < full <= 64 << 20
+    kw = dict(wfmt=wfmt, max_batch=b, max_seq=s, n_weight_slots=1)
+    p = plan(OPT30, **kw)
+    small = plan(OPT30, **kw, hbm_budget_bytes=p["hbm_bytes"] - 1)
+    assert p["hbm_bytes"] - small["hbm_bytes"] == full - decode
+    assert plan(OPT30, **kw, hbm_budget_bytes=p["hbm_bytes"]) == p
+    # the same choice one byte short of the whole workspace, and none short of both
+    kw4 = (c_shape(OPT30), w, 0, b, s)
+    me = min(q["hbm_bytes"] for _, q in candidates(OPT30, wfmt, "fp16", b, s))
+    pol, got = B.pipo_configure(*kw4, me - 1, 512 * GB)
+    assert got["hbm_bytes"] == me - (full - decode) and pol.n_weight_slots == 1
+    with pytest.raises(B.PipoError) as e:
+        B.pipo_configure(*kw4, me - (full - decode) - 1, 512 * GB)
+    assert B.STATUS_NAMES[e.value.status] == "PIPO_ERR_OOM_DEVICE"
