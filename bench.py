@@ -124,7 +124,7 @@ def gemm_symbols(M, N, K, epi, w4, frag):
         if K >= 1536:
             S = _split_k(-(-N // (16 * cfg[1] * cfg[2])), K, 256)
     args = ", ".join(str(v) for v in cfg)
-    syms = [f"gemm_slab<{args}, {b}, {epi}, {pk}>(GemmArgs, float*, long)"]
+    syms = [f"gemm_slab<{args}, {b}, {epi}, {pk}, true>(GemmArgs, float*, long)"]
     if w4 and not frag and cfg == (2, 2, 4, 4, 2):    # row-major INT4: the streaming kernel
         pd, kc = (2, 256) if K % (256 * S) == 0 else (4, 128)
         syms = [f"gemm_stream_w4<{pd}, {kc}, {epi}>(GemmArgs, float*, long)"]

@@ -52,9 +52,11 @@ enum { PIPO_EPI_F16 = 0, PIPO_EPI_RELU_F16 = 1, PIPO_EPI_ADD_F32 = 2, PIPO_EPI_F
  * them in a fixed order and applies the epilogue.  With less (or NULL)
  * workspace the GEMM takes the tiles that run best with the K ranges that
  * fit, or unsplit; the result is the same up to rounding.  Calls sharing a workspace must not
- * overlap in time.  For a given (M, N, K, wfmt, epilogue) and room in the
- * workspace the summation order is fixed, so repeated calls give the same
- * bits.
+ * overlap in time.  Operands run fastest with X and the weights on 16-byte
+ * boundaries and the (scale, min) pairs on 4-byte ones; any other address is
+ * taken too.  For a given (M, N, K, wfmt, layout, epilogue), alignment and
+ * room in the workspace the summation order is fixed, so repeated calls give
+ * the same bits.
  */
 pipo_status pipo_op_gemm_f16(const uint16_t* X, const uint16_t* W, const uint16_t* bias,
                              void* out, int64_t M, int64_t N, int64_t K, int32_t epi,

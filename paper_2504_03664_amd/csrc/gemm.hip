@@ -18,8 +18,8 @@
 //     128 x 64 fed by global -> LDS loads through rings of LDS stages; INT4
 //     codes reach LDS the same way and are expanded there, once per tile;
 //     fp16 may split K like gemm_slab.
-//   * gemm_tiled (M > 16 and operands that are not 16-byte aligned, or fp16
-//     prefill with few big tiles that cannot be split): 128 x 128 output tiles, K staged through registers into double-buffered LDS in
+//   * gemm_tiled (prefill with operands that are not 16-byte aligned, or fp16
+//     with few big tiles that cannot be split): 128 x 128 output tiles, K staged through registers into double-buffered LDS in
 //     steps of 64, 4 waves of 64 x 64; tiles ordered per XCD so that each
 //     XCD's L2 serves a compact block.
 // The decode kernels read each weight once per pass and do so with
@@ -372,8 +372,8 @@ void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStrea
 }
 
 // ---------------------------------------------------------------------------
-// tiled GEMM (operands off 16-byte alignment, and fp16 prefill with few big
-// tiles that cannot be split: see plan_prefill)
+// tiled GEMM (prefill with operands off 16-byte alignment, and fp16 prefill with
+// few big tiles that cannot be split: see plan_prefill)
 constexpr int kTBM = 128, kTBN = 128, kTBK = 64, kTPad = 8;
 constexpr int kTThreads = 256;  // 2 x 2 waves of 64 x 64
 constexpr int kTGroupM = 4;
@@ -1091,11 +1091,13 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
     // row-major INT4 at M <= 32: see gemm_stream_w4 (same K ranges)
     if (W4 && !PK && p.kernel == kSlab && p.slab == kW4M32n128) p.kernel = kStreamW4;
     // loads straight into LDS take 16 bytes at a time: operands off that
-    // alignment go to the kernels that load through registers
+    // alignment go through registers, in decode by the same plan
     const uintptr_t at = reinterpret_cast<uintptr_t>(a.X) |
                          (W4 ? reinterpret_cast<uintptr_t>(a.Wq) : reinterpret_cast<uintptr_t>(a.W));
-    if (at % 16 != 0 || (W4 && reinterpret_cast<uintptr_t>(a.Wsm) % 4 != 0))
-      p = GemmPlan{a.M <= kSkinnyMaxM ? kSkinny : kTiled};
+    const bool direct =
+        at % 16 == 0 && (!W4 || reinterpret_cast<uintptr_t>(a.Wsm) % 4 == 0);
+    if (!direct && a.M <= kSkinnyMaxM) p = GemmPlan{kSkinny};
+    if (!direct && a.M > kDecodeMaxM) p = GemmPlan{kTiled};
     switch (p.kernel) {
       case kSkinny:
         // 64 W rows per workgroup (less X traffic per W byte) once that still
@@ -1106,7 +1108,7 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
           launch_skinny<1, W4, EPI, PK>(a, st);
         break;
       case kSlab:
-        (W4 ? launch_slab_w4 : launch_slab_f16)(a, EPI, p.slab, p.splits, ws, st);
+        (W4 ? launch_slab_w4 : launch_slab_f16)(a, EPI, p.slab, direct, p.splits, ws, st);
         break;
       case kStreamW4:
         if constexpr (W4 && !PK) launch_stream_w4<EPI>(a, p.splits, ws, st);

@@ -122,8 +122,9 @@ void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStrea
 
 // Slab kernels (gemm_slab.h) by index into the tables below, PIPO_SLAB_F16
 // in gemm_slab_f16.hip and PIPO_SLAB_W4 in gemm_slab_w4.hip; S K ranges
-// (S > 1: partials to ws, without the merge).  X and the weights must be
-// 16-byte aligned, a (scale, min) pair 4-byte aligned, K % (64 S) == 0.
+// (S > 1: partials to ws, without the merge), K % (64 S) == 0.  direct: X and
+// the weights are 16-byte aligned, the (scale, min) pairs 4-byte aligned; it
+// must be so for MF = 1 and for 256 columns.
 //      index, MF, NF, WN, KS, PD   (tile 16 MF x 16 NF WN, WN KS waves)
 #define PIPO_SLAB_F16(X)                                                                \
   X(0, 1, 1, 1, 8, 3) X(1, 1, 2, 1, 8, 2)                                               \
@@ -136,7 +137,9 @@ void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStrea
   X(1, 2, 2, 2, 4, 3) X(2, 2, 2, 4, 4, 2)                                               \
   X(3, 4, 2, 2, 4, 2) X(4, 4, 4, 2, 4, 2)                                               \
   X(5, 8, 2, 2, 4, 1) X(6, 8, 2, 4, 2, 2) X(7, 8, 4, 4, 2, 2) X(8, 8, 2, 8, 1, 3)
-void launch_slab_f16(const GemmArgs& a, int epi, int idx, int S, float* ws, hipStream_t st);
-void launch_slab_w4(const GemmArgs& a, int epi, int idx, int S, float* ws, hipStream_t st);
+void launch_slab_f16(const GemmArgs& a, int epi, int idx, bool direct, int S, float* ws,
+                     hipStream_t st);
+void launch_slab_w4(const GemmArgs& a, int epi, int idx, bool direct, int S, float* ws,
+                    hipStream_t st);
 
 }  // namespace pipo

@@ -68,7 +68,11 @@ __device__ __forceinline__ void wait_stages(int left) {
   }
 }
 
-template <int MF, int NF, int WN, int KS, int PD, bool W4, int EPI, bool PK>
+// DIRECT: operands aligned as loads into LDS need (16 bytes, a (scale, min)
+// pair 4); others come through registers, one slab ahead (fp16 row-major M = 64,
+// 4096 x 14336: 36 us, with DIRECT 28; through 128 x 128 tiles without K ranges
+// 264; INT4 58 with the register-staged kernel before this one, 34 here)
+template <int MF, int NF, int WN, int KS, int PD, bool W4, int EPI, bool PK, bool DIRECT>
 __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* part, int64_t kper) {
   using C = SlabCfg<MF, NF, WN, KS, PD, W4>;
   constexpr int KC = C::KC;
@@ -145,14 +149,16 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
       ssrc[i] = reinterpret_cast<const uint8_t*>(a.Wsm) + w4_sm<PK>(n, 0, K) * 4;
     }
   }
-  const auto issue = [&](int t, int slot) {
+  // the loads of stage t, each with its number and its place in slot `slot`:
+  // x(number, source, place) and w(..) of 16 bytes a lane, s(..) of 4
+  const auto stage = [&](int t, int slot, auto x, auto w, auto s) {
     uint8_t* st = lds + slot * C::kStage;
     const int klast = (int)kper - 64;
 #pragma unroll
     for (int i = 0; i < C::kXLoads; ++i) {
       const int p = wave * C::kXLoads + i;
       const int k = chunk_of(t, p / (2 * MF)) * KC;
-      lds_dma16(xsrc[i] + (k < klast ? k : klast), st + p * 1024);
+      x(i, xsrc[i] + (k < klast ? k : klast), st + p * 1024);
     }
     const int c = chunk_of(t, ks);
     const int64_t k = kbeg + (int64_t)(c < nch ? c : nch - 1) * KC;
@@ -160,21 +166,51 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
     if constexpr (W4) {
       const int64_t off = PK ? (k >> 7) * 1024 + ((k >> 6) & 1) * 512 : k / 2;
 #pragma unroll
-      for (int f = 0; f < WSRC; ++f) lds_dma16_w<NT>(wsrc[f] + off, wb + f * 1024);
+      for (int f = 0; f < WSRC; ++f) w(f, wsrc[f] + off, wb + f * 1024);
       const int64_t soff = PK ? (k >> 7) * 128 + ((k >> 6) & 1) * 4 : k / 64 * 4;
 #pragma unroll
       for (int i = 0; i < C::kSmLoads; ++i)
-        lds_dma4(ssrc[i] + soff, wb + C::kWBlocks * 1024 + i * 256);
+        s(i, ssrc[i] + soff, wb + C::kWBlocks * 1024 + i * 256);
     } else if constexpr (PK) {
 #pragma unroll
       for (int f = 0; f < NF; ++f)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-          lds_dma16_w<NT>(wsrc[f] + ((k >> 5) + i) * 1024, wb + (2 * f + i) * 1024);
+          w(2 * f + i, wsrc[f] + ((k >> 5) + i) * 1024, wb + (2 * f + i) * 1024);
     } else {
 #pragma unroll
-      for (int f = 0; f < 2 * NF; ++f) lds_dma16_w<NT>(wsrc[f] + k * 2, wb + f * 1024);
+      for (int f = 0; f < 2 * NF; ++f) w(f, wsrc[f] + k * 2, wb + f * 1024);
     }
+  };
+  const auto issue = [&](int t, int slot) {
+    stage(
+        t, slot, [](int, const void* g, uint8_t* to) { lds_dma16(g, to); },
+        [](int, const void* g, uint8_t* to) { lds_dma16_w<NT>(g, to); },
+        [](int, const void* g, uint8_t* to) { lds_dma4(g, to); });
+  };
+  // !DIRECT: a stage from memory into registers, and from there into a slot
+  u32x4 xreg[C::kXLoads], wreg[C::kWBlocks];
+  uint32_t sreg[C::kSmLoads + 1];
+  const auto fetch = [&](int t) {
+    stage(
+        t, 0, [&](int i, const void* g, uint8_t*) { xreg[i] = *static_cast<const u32x4*>(g); },
+        [&](int i, const void* g, uint8_t*) {
+          wreg[i] = NT ? load_u32x4_stream(g) : *static_cast<const u32x4*>(g);
+        },
+        [&](int i, const void* g, uint8_t*) { sreg[i] = *static_cast<const uint32_t*>(g); });
+  };
+  const auto put = [&](int slot) {
+    stage(
+        0, slot,
+        [&](int i, const void*, uint8_t* to) {
+          *reinterpret_cast<u32x4*>(to + lane * 16) = xreg[i];
+        },
+        [&](int i, const void*, uint8_t* to) {
+          *reinterpret_cast<u32x4*>(to + lane * 16) = wreg[i];
+        },
+        [&](int i, const void*, uint8_t* to) {
+          *reinterpret_cast<uint32_t*>(to + lane * 4) = sreg[i];
+        });
   };
   f4 sums[kSums][NF][MF];
 #pragma unroll
@@ -231,27 +267,41 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
     }
   };
 
-#pragma unroll
-  for (int p = 0; p < PD; ++p)
-    if (p < nr) issue(p, p);
-  int slot = 0;
-  for (int t = 0; t < nr; ++t) {
-    __builtin_amdgcn_sched_barrier(0);
-    wait_stages<C::kOps, PD - 1>(nr - 1 - t);  // this wave's loads of stage t landed
-    __builtin_amdgcn_s_barrier();              // everyone's did, and stage t - 1 is read
-    __builtin_amdgcn_sched_barrier(0);
-    if (t + PD < nr) issue(t + PD, slot == 0 ? PD : slot - 1);
-    if (chunk_of(t, ks) < nch) {
-      if constexpr (kSums == 2) {
-        if ((t >> 1) & 1)
-          compute(slot, std::integral_constant<int, kSums - 1>{});
-        else
-          compute(slot, std::integral_constant<int, 0>{});
-      } else {
+  const auto round = [&](int t, int slot) {
+    if (chunk_of(t, ks) >= nch) return;
+    if constexpr (kSums == 2) {
+      if ((t >> 1) & 1)
+        compute(slot, std::integral_constant<int, kSums - 1>{});
+      else
         compute(slot, std::integral_constant<int, 0>{});
-      }
+    } else {
+      compute(slot, std::integral_constant<int, 0>{});
     }
-    slot = slot == PD ? 0 : slot + 1;
+  };
+  if constexpr (DIRECT) {
+#pragma unroll
+    for (int p = 0; p < PD; ++p)
+      if (p < nr) issue(p, p);
+    int slot = 0;
+    for (int t = 0; t < nr; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      wait_stages<C::kOps, PD - 1>(nr - 1 - t);  // this wave's loads of stage t landed
+      __builtin_amdgcn_s_barrier();              // everyone's did, and stage t - 1 is read
+      __builtin_amdgcn_sched_barrier(0);
+      if (t + PD < nr) issue(t + PD, slot == 0 ? PD : slot - 1);
+      round(t, slot);
+      slot = slot == PD ? 0 : slot + 1;
+    }
+  } else {
+    fetch(0);
+    put(0);
+    if (nr > 1) fetch(1);
+    for (int t = 0; t < nr; ++t) {
+      __syncthreads();  // stage t is in its slot, and stage t - 1 is read
+      if (t + 1 < nr) put((t + 1) & 1);
+      if (t + 2 < nr) fetch(t + 2);
+      round(t, t & 1);
+    }
   }
 
   // element j of fragment (f, mf): W row 16 f + 4 g + j, X row 16 mf + r
@@ -316,28 +366,39 @@ __global__ __launch_bounds__(WN * KS * 64) void gemm_slab(GemmArgs a, float* par
 }
 
 template <int MF, int NF, int WN, int KS, int PD, bool W4, int EPI>
-static void launch_slab_epi(const GemmArgs& a, int S, float* ws, hipStream_t st) {
+static void launch_slab_epi(const GemmArgs& a, bool direct, int S, float* ws, hipStream_t st) {
   using C = SlabCfg<MF, NF, WN, KS, PD, W4>;
   const int64_t tm = (a.M + C::kRows - 1) / C::kRows, tn = (a.N + C::kCols - 1) / C::kCols;
   // several row tiles: whole rounds over the XCDs (the kernel drops the excess)
   const int64_t wgs = tm == 1 ? tn : (tm * tn + kXcds - 1) / kXcds * kXcds;
   const dim3 grid((unsigned)wgs, (unsigned)S);
+  const auto go = [&](auto kernel) {
+    launch(kernel, grid, dim3(C::kThreads), 0, st, a, ws, a.K / S);
+  };
+  // (M <= 16 and the widest tiles are for aligned operands only)
+  if constexpr (MF > 1 && C::kCols < 256) {
+    if (!direct)
+      return a.packed ? go(gemm_slab<MF, NF, WN, KS, PD, W4, EPI, true, false>)
+                      : go(gemm_slab<MF, NF, WN, KS, PD, W4, EPI, false, false>);
+  }
   if (a.packed)
-    launch((gemm_slab<MF, NF, WN, KS, PD, W4, EPI, true>), grid, dim3(C::kThreads), 0, st, a, ws,
-           a.K / S);
+    go(gemm_slab<MF, NF, WN, KS, PD, W4, EPI, true, true>);
   else
-    launch((gemm_slab<MF, NF, WN, KS, PD, W4, EPI, false>), grid, dim3(C::kThreads), 0, st, a, ws,
-           a.K / S);
+    go(gemm_slab<MF, NF, WN, KS, PD, W4, EPI, false, true>);
 }
 
 template <int MF, int NF, int WN, int KS, int PD, bool W4>
-static void launch_slab(const GemmArgs& a, int epi, int S, float* ws, hipStream_t st) {
+static void launch_slab(const GemmArgs& a, int epi, bool direct, int S, float* ws,
+                        hipStream_t st) {
+  const auto go = [&](auto e) {
+    launch_slab_epi<MF, NF, WN, KS, PD, W4, decltype(e)::value>(a, direct, S, ws, st);
+  };
   switch (epi) {
-    case EPI_F16: return launch_slab_epi<MF, NF, WN, KS, PD, W4, EPI_F16>(a, S, ws, st);
-    case EPI_RELU_F16: return launch_slab_epi<MF, NF, WN, KS, PD, W4, EPI_RELU_F16>(a, S, ws, st);
-    case EPI_ADD_F32: return launch_slab_epi<MF, NF, WN, KS, PD, W4, EPI_ADD_F32>(a, S, ws, st);
-    case EPI_F32: return launch_slab_epi<MF, NF, WN, KS, PD, W4, EPI_F32>(a, S, ws, st);
-    default: return launch_slab_epi<MF, NF, WN, KS, PD, W4, EPI_QKV>(a, S, ws, st);
+    case EPI_F16: return go(std::integral_constant<int, EPI_F16>{});
+    case EPI_RELU_F16: return go(std::integral_constant<int, EPI_RELU_F16>{});
+    case EPI_ADD_F32: return go(std::integral_constant<int, EPI_ADD_F32>{});
+    case EPI_F32: return go(std::integral_constant<int, EPI_F32>{});
+    default: return go(std::integral_constant<int, EPI_QKV>{});
   }
 }
 

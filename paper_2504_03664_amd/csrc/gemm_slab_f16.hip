@@ -4,10 +4,11 @@
 
 namespace pipo {
 
-void launch_slab_f16(const GemmArgs& a, int epi, int idx, int S, float* ws, hipStream_t st) {
+void launch_slab_f16(const GemmArgs& a, int epi, int idx, bool direct, int S, float* ws,
+                     hipStream_t st) {
   switch (idx) {
 #define PIPO_CASE(i, MF, NF, WN, KS, PD) \
-  case i: return launch_slab<MF, NF, WN, KS, PD, false>(a, epi, S, ws, st);
+  case i: return launch_slab<MF, NF, WN, KS, PD, false>(a, epi, direct, S, ws, st);
     PIPO_SLAB_F16(PIPO_CASE)
 #undef PIPO_CASE
   }

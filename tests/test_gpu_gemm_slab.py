@@ -105,3 +105,40 @@ def test_gemm_partial_workspace_exact(M, N, K, w4):
                  dWs.ptr if nbytes else None, nbytes)
             B.pipo_dev_synchronize()
             assert np.array_equal(dO.to_array(np.float32, (M, N)).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("M,N,K", [(20, 80, 2048), (32, 8320, 2048), (32, 24592, 256),
+                                   (20, 144, 16384), (33, 80, 384), (64, 24592, 128),
+                                   (64, 144, 16384), (65, 80, 640), (100, 16400, 128),
+                                   (127, 144, 2048), (128, 144, 16384)])
+@pytest.mark.parametrize("w4", [False, True])
+def test_gemm_unaligned_decode_exact(M, N, K, w4):
+    """Every decode configuration with X two bytes, W eight bytes or the
+    (scale, min) pairs two bytes past their alignment, with K ranges and
+    without."""
+    X, W, q, want = _case(M, N, K, w4)
+    full = B.pipo_op_gemm_workspace_bytes(M, N, K, B.PIPO_W_INT4_G64 if w4 else B.PIPO_W_FP16)
+    dO, dWs = DB(M * N * 4), DB(max(full, 16))
+
+    def shifted(x, nbytes):
+        return DB.from_array(np.concatenate([np.zeros(nbytes, np.uint8),
+                                             np.ascontiguousarray(x).view(np.uint8).reshape(-1)]))
+
+    for frag in (False, True):
+        if w4:
+            mats = B.pipo_pack_w4(*q) if frag else q
+            call = B.pipo_op_gemm_w4_frag if frag else B.pipo_op_gemm_w4
+        else:
+            W16 = W.astype(np.float16)
+            mats = (B.pipo_pack_f16(W16) if frag else W16,)
+            call = B.pipo_op_gemm_f16_frag if frag else B.pipo_op_gemm_f16
+        for shifts in ((2, 0, 0), (0, 8, 0), (0, 0, 2))[:3 if w4 else 2]:
+            dX = shifted(X.astype(np.float16), shifts[0])
+            ops = [shifted(m, s) for m, s in zip(mats, shifts[1:])]
+            for nbytes in {full, 0}:
+                print(f"gemm unaligned {shifts} M={M} N={N} K={K} w4={w4} frag={frag} ws={nbytes}",
+                      flush=True)
+                call(dX.ptr + shifts[0], *[o.ptr + s for o, s in zip(ops, shifts[1:])], None,
+                     dO.ptr, M, N, K, B.PIPO_EPI_F32, dWs.ptr if nbytes else None, nbytes)
+                B.pipo_dev_synchronize()
+                assert np.array_equal(dO.to_array(np.float32, (M, N)).astype(np.float64), want)
