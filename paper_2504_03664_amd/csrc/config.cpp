@@ -362,56 +362,51 @@ pipo_status pipo_configure(const pipo_shape* shape, int32_t wfmt, int32_t kv_fmt
   // resident or streamed, streamed layers in host memory or on disk, KV
   // resident or in host memory) and the two pipelines, take the one that
   // streams the fewest bytes per decode step; at equal bytes host memory
-  // before disk, then the performance-optimized pipeline (more slots).
+  // before disk, then the performance-optimized pipeline, then room for the
+  // prefill's whole GEMM workspace (hbm_plan; a third slot measures 0.3 to 1 %
+  // of decode, the workspace up to half of a short prompt's products), then
+  // more slots.
   pipo_policy best{};
-  int64_t best_bytes = -1, best_slots = 0, need_hbm = -1, need_host = -1;
-  int best_disk = 0;
+  int64_t best_bytes = -1, need_hbm = -1, need_host = -1;
+  int best_rank = 0;
   pipo_status first_err = PIPO_OK;
-  // First with the prefill's whole GEMM workspace; where nothing fits, with as
-  // much as the budget leaves (hbm_plan).
-  for (const int64_t budget : {(int64_t)0, hbm}) {
-    if (best_bytes >= 0) break;
-    for (int w_host = 0; w_host <= 1; ++w_host)
-      for (int on_disk = 0; on_disk <= (w_host && disk > 0 ? 1 : 0); ++on_disk)
-        for (int e_host = 0; e_host <= 1; ++e_host)
-          for (int kv_host = 0; kv_host <= w_host; ++kv_host)
-            for (int slots : {3, 2, 1}) {
-              if (!w_host && !e_host && slots != 3) continue;  // nothing streams: slots unused
-              pipo_policy pol{};
-              pol.wfmt = wfmt;
-              pol.kv_fmt = kv_fmt;
-              pol.weights_on_host = w_host;
-              pol.weights_on_disk = on_disk;
-              pol.embed_on_host = e_host;
-              pol.kv_on_host = kv_host;
-              pol.n_weight_slots = slots;
-              pol.max_batch = max_batch;
-              pol.max_seq = max_seq;
-              const pipo_status st = normalize_policy(shape, &pol);
-              if (st != PIPO_OK) {
-                if (first_err == PIPO_OK) first_err = st;
-                continue;
-              }
-              pol.hbm_budget_bytes = budget;
-              const int64_t h = hbm_plan(*shape, pol).total();
-              const int64_t k = host_kv_bytes(*shape, pol) + host_weight_bytes(*shape, pol);
-              if (need_hbm < 0 || h < need_hbm) need_hbm = h;
-              if (h > hbm) continue;
-              if (need_host < 0 || k < need_host) need_host = k;  // among those that fit in HBM
-              if (k > host || disk_file_bytes(*shape, pol) > disk) continue;
-              const int64_t bytes = step_bytes(*shape, pol);
-              const bool better =
-                  best_bytes < 0 || bytes < best_bytes ||
-                  (bytes == best_bytes &&
-                   (on_disk < best_disk || (on_disk == best_disk && slots > best_slots)));
-              if (better) {
-                best = pol;
-                best_bytes = bytes;
-                best_slots = slots;
-                best_disk = on_disk;
-              }
+  for (int w_host = 0; w_host <= 1; ++w_host)
+    for (int on_disk = 0; on_disk <= (w_host && disk > 0 ? 1 : 0); ++on_disk)
+      for (int e_host = 0; e_host <= 1; ++e_host)
+        for (int kv_host = 0; kv_host <= w_host; ++kv_host)
+          for (int slots : {3, 2, 1}) {
+            if (!w_host && !e_host && slots != 3) continue;  // nothing streams: slots unused
+            pipo_policy pol{};
+            pol.wfmt = wfmt;
+            pol.kv_fmt = kv_fmt;
+            pol.weights_on_host = w_host;
+            pol.weights_on_disk = on_disk;
+            pol.embed_on_host = e_host;
+            pol.kv_on_host = kv_host;
+            pol.n_weight_slots = slots;
+            pol.max_batch = max_batch;
+            pol.max_seq = max_seq;
+            const pipo_status st = normalize_policy(shape, &pol);
+            if (st != PIPO_OK) {
+              if (first_err == PIPO_OK) first_err = st;
+              continue;
             }
-  }
+            const bool whole_ws = hbm_plan(*shape, pol).total() <= hbm;
+            pol.hbm_budget_bytes = hbm;
+            const int64_t h = hbm_plan(*shape, pol).total();
+            const int64_t k = host_kv_bytes(*shape, pol) + host_weight_bytes(*shape, pol);
+            if (need_hbm < 0 || h < need_hbm) need_hbm = h;
+            if (h > hbm) continue;
+            if (need_host < 0 || k < need_host) need_host = k;  // among those that fit in HBM
+            if (k > host || disk_file_bytes(*shape, pol) > disk) continue;
+            const int64_t bytes = step_bytes(*shape, pol);
+            const int rank = (on_disk ? 0 : 16) + (slots >= 2 ? 8 : 0) + (whole_ws ? 4 : 0) + slots;
+            if (best_bytes < 0 || bytes < best_bytes || (bytes == best_bytes && rank > best_rank)) {
+              best = pol;
+              best_bytes = bytes;
+              best_rank = rank;
+            }
+          }
   if (best_bytes < 0) {
     if (first_err != PIPO_OK && need_hbm < 0) return first_err;
     if (need_host < 0) {
@@ -424,7 +419,6 @@ pipo_status pipo_configure(const pipo_shape* shape, int32_t wfmt, int32_t kv_fmt
               (long long)need_host, (long long)host, (long long)disk);
     return PIPO_ERR_OOM_HOST;
   }
-  best.hbm_budget_bytes = hbm;
   *policy_out = best;
   if (plan_out) fill_plan(*shape, best, plan_out);
   return PIPO_OK;

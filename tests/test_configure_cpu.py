@@ -190,3 +190,21 @@ def test_plan_holds_every_prefill_gemm_workspace(wfmt):
     with pytest.raises(B.PipoError) as e:
         B.pipo_configure(*kw4, me - (full - decode) - 1, 512 * GB)
     assert B.STATUS_NAMES[e.value.status] == "PIPO_ERR_OOM_DEVICE"
+
+
+def test_configure_streams_nothing_more_for_the_prefill_workspace():
+    """Every placement is chosen from its smallest memory on, that with the
+    GEMM workspace of decode: a budget one byte short of the prefill's does not
+    send layers, head or KV cache to the host, nor the pipeline to one slot;
+    a third slot gives way to the workspace."""
+    b, s, host = 1, 700, 512 * GB
+    extra = _gemm_ws(OPT30, 0, b * s) - _gemm_ws(OPT30, 0, 128)
+    assert extra > 0
+    every = list(candidates(OPT30, "fp16", "fp16", b, s))
+    for _, p in every:
+        for hbm in (p["hbm_bytes"] - 1, p["hbm_bytes"] - extra):
+            best = max((-q["h2d_bytes_per_step"], c["n_weight_slots"] >= 2, q["hbm_bytes"] <= hbm,
+                        c["n_weight_slots"]) for c, q in every if q["hbm_bytes"] - extra <= hbm)
+            pol, got = B.pipo_configure(c_shape(OPT30), 0, 0, b, s, hbm, host)
+            assert got["hbm_bytes"] <= hbm
+            assert (-got["h2d_bytes_per_step"], pol.n_weight_slots) == (best[0], best[3])
