@@ -40,7 +40,8 @@ __device__ __forceinline__ float group_min8(float v) {
 // The division is 32-bit where the pieces allow (64-bit took a third of the
 // quantizer's time).
 __device__ __forceinline__ bool piece_of(int64_t rows, int64_t d, int64_t& r, int& c) {
-  const int64_t per_row = d / 8, e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t per_row = d / 8;
+  const int64_t e = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
   if (e >= rows * per_row) return false;
   if (rows * per_row < ((int64_t)1 << 32)) {
     const uint32_t row = (uint32_t)e / (uint32_t)per_row;
@@ -107,6 +108,14 @@ __global__ __launch_bounds__(256) void kv_dequant_k(const uint8_t* __restrict__ 
   *reinterpret_cast<h8*>(y + r * d + 8 * c) = dequant8_fp8(codes, s2, m2);
 }
 
+// a thread per 8 elements, up to 2^30 threads (a launch takes under 2^32 in a
+// dimension) in each row of the grid; piece_of drops the excess
+static dim3 piece_grid(int64_t pieces) {
+  const int64_t blocks = (pieces + 255) / 256, row = (int64_t)1 << 22;
+  return blocks <= row ? dim3((unsigned)blocks)
+                       : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
+}
+
 pipo_status launch_kv_quant(const uint16_t* x, uint8_t* out, int64_t rows, int64_t d,
                             hipStream_t st) {
   if (rows < 0 || d <= 0 || d % 256 != 0) {
@@ -116,7 +125,7 @@ pipo_status launch_kv_quant(const uint16_t* x, uint8_t* out, int64_t rows, int64
   }
   const int64_t n = rows * (d / 8);
   if (n == 0) return PIPO_OK;
-  launch(kv_quant_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, out, rows, d);
+  launch(kv_quant_k, piece_grid(n), dim3(256), 0, st, x, out, rows, d);
   PIPO_HIP_TRY(hipGetLastError());
   return PIPO_OK;
 }
@@ -130,7 +139,7 @@ pipo_status launch_kv_dequant(const uint8_t* in, uint16_t* y, int64_t rows, int6
   }
   const int64_t n = rows * (d / 8);
   if (n == 0) return PIPO_OK;
-  launch(kv_dequant_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, in, y, rows, d);
+  launch(kv_dequant_k, piece_grid(n), dim3(256), 0, st, in, y, rows, d);
   PIPO_HIP_TRY(hipGetLastError());
   return PIPO_OK;
 }

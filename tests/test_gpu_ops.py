@@ -341,6 +341,45 @@ def test_kv_quant_dequant_bit_exact_vs_oracle(rows, d):
     assert np.array_equal(back, dequant_int4_g64(codes, sm, np.float64).astype(np.float16))
 
 
+def test_kv_quant_dequant_above_2e35_elements():
+    """Rows on both sides of the borders of the grid (2^30 threads in a row of
+    it, 2^32 in a launch dimension) of a 64 GiB matrix, against the oracle."""
+    rows, d = (1 << 15) + 1, 1 << 20
+    log(f"kv quant rows={rows} d={d}")
+    at = [0, (1 << 13) - 1, 1 << 13, (1 << 15) - 1, 1 << 15]
+    x = _kv_test_rows(np.random.default_rng(35), len(at), d)
+    codes, sm = quant_kv_int4_g64(x)
+    want = _kv_rows(codes, sm)
+    back = dequant_int4_g64(codes, sm, np.float64).astype(np.float16)
+    q_row = want.shape[1]
+
+    def put(buf, i, row):
+        B._check(B.lib().pipo_copy_h2d(buf.ptr + at[i] * row.nbytes, B._ptr(row), row.nbytes), "h2d")
+
+    def get(buf, i, like):
+        row = np.empty_like(like)
+        B._check(B.lib().pipo_copy_d2h(B._ptr(row), buf.ptr + at[i] * row.nbytes, row.nbytes), "d2h")
+        return row
+
+    dx, dq = DB(rows * d * 2), DB(rows * q_row)
+    try:
+        for i in range(len(at)):
+            put(dx, i, np.ascontiguousarray(x[i]))
+            put(dq, i, np.zeros(q_row, np.uint8))
+        B.pipo_op_kv_quant(dx.ptr, dq.ptr, rows, d)
+        B.pipo_dev_synchronize()
+        for i in range(len(at)):
+            assert np.array_equal(get(dq, i, want[i]), want[i]), f"row {at[i]}"
+            put(dx, i, np.zeros(d, np.float16))
+        B.pipo_op_kv_dequant(dq.ptr, dx.ptr, rows, d)
+        B.pipo_dev_synchronize()
+        for i in range(len(at)):
+            assert np.array_equal(get(dx, i, back[i]), back[i]), f"row {at[i]}"
+    finally:
+        dx.free()
+        dq.free()
+
+
 @pytest.mark.parametrize("b,T,H,D", [(1, 1, 4, 64), (3, 70, 4, 128), (2, 1000, 2, 128),
                                      (16, 543, 8, 64), (4, 600, 56, 128), (3, 129, 6, 128),
                                      (2, 300, 12, 64)])
