@@ -197,7 +197,8 @@ __global__ __launch_bounds__(256) void attn_decode_kv4_k(const uint16_t* __restr
   // head group) pairs: the head groups of a sequence share the lines at their
   // borders and those of the (scale, min) pairs, which then meet in one L2
   const int groups = H / HP;
-  const int64_t pair = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int64_t id = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
+  const int64_t pair = id % 8 * ((int64_t)gridDim.x / 8 * gridDim.z) + id / 8;
   if (pair >= (int64_t)groups * b) return;
   const int bi = (int)(pair / groups), kb = (int)(pair - (int64_t)bi * groups);
   const int sp = blockIdx.y, S = gridDim.y;
@@ -708,7 +709,11 @@ static void launch_decode_mha(const uint16_t* q, const void* kc, const void* vc,
                               int b, int H, int t, bool kv4, int S, int chunk, float* workspace,
                               hipStream_t st) {
   const dim3 grid((unsigned)(H / HP), (unsigned)b, (unsigned)S);
-  const dim3 grid4((unsigned)(((int64_t)(H / HP) * b + 7) / 8 * 8), (unsigned)S);
+  // INT4: the pairs in one dimension, with rows of 2^22 workgroups beyond that (a
+  // launch takes under 2^32 threads in a dimension)
+  const int64_t pairs = ((int64_t)(H / HP) * b + 7) / 8 * 8;
+  const int64_t row = std::min(pairs, (int64_t)1 << 22);
+  const dim3 grid4((unsigned)row, (unsigned)S, (unsigned)((pairs + row - 1) / row));
   if (kv4)
     launch(attn_decode_kv4_k<D, HP>, grid4, dim3(256), 0, st, q, kc, vc, o, workspace, b, H, t,
            chunk);

@@ -341,6 +341,35 @@ def test_kv_quant_dequant_bit_exact_vs_oracle(rows, d):
     assert np.array_equal(back, dequant_int4_g64(codes, sm, np.float64).astype(np.float16))
 
 
+def test_attn_decode_kv4_above_2e24_head_groups():
+    """65535 sequences of 257 groups of four heads, more workgroups of 256
+    threads than a launch dimension takes; one position, so that the output
+    is the expanded value rounded to fp32 and to fp16."""
+    b, H, D = 65535, 1028, 64
+    log(f"kv4 decode attention b={b} H={H} D={D}")
+    d, row = H * D, H * D // 2 + H * D // 16
+    x = _kv_test_rows(np.random.default_rng(24), 3, d)
+    codes, sm = quant_kv_int4_g64(x)
+    rows, want = _kv_rows(codes, sm), dequant_int4_g64(codes, sm, np.float64).astype(np.float16)
+    at = [0, b // 2, b - 1]
+    dq, dk, dv, do = DB(b * d * 2), DB(b * row), DB(b * row), DB(b * d * 2)
+    try:
+        zero = np.zeros(d, np.float16)
+        for i, s in enumerate(at):
+            for buf, a in ((dq, zero), (dk, rows[i]), (dv, rows[i]), (do, zero)):
+                B._check(B.lib().pipo_copy_h2d(buf.ptr + s * a.nbytes, B._ptr(a), a.nbytes), "h2d")
+        B.pipo_op_attn_decode_kv4(dq.ptr, dk.ptr, dv.ptr, do.ptr, b, H, D, 0)
+        B.pipo_dev_synchronize()
+        for i, s in enumerate(at):
+            got = np.empty(d, np.float16)
+            B._check(B.lib().pipo_copy_d2h(B._ptr(got), do.ptr + s * got.nbytes, got.nbytes), "d2h")
+            w = want[i].astype(np.float64)
+            assert (np.abs(got - w) <= 2.0 ** -10 * np.abs(w) + 2.0 ** -24).all(), f"sequence {s}"
+    finally:
+        for buf in (dq, dk, dv, do):
+            buf.free()
+
+
 def test_kv_quant_dequant_above_2e35_elements():
     """Rows on both sides of the borders of the grid (2^30 threads in a row of
     it, 2^32 in a launch dimension) of a 64 GiB matrix, against the oracle."""
