@@ -13,7 +13,8 @@
 //     loads several stages ahead; K split over waves, and over workgroups
 //     whose fp32 partial sums go to a workspace that gemm_combine adds up in
 //     a fixed order.
-//   * gemm_stream_w4 (16 < M <= 32, row-major INT4 W).
+//   * gemm_stream_w4 (16 < M <= 32, row-major INT4 W with N above 4096 and a long
+//     K, or above 16384).
 //   * gemm_big_f16 / gemm_big_w4 (prefill with 256 x 256 tiles): 8 waves of
 //     128 x 64 fed by global -> LDS loads through rings of LDS stages; INT4
 //     codes reach LDS the same way and are expanded there, once per tile;
@@ -179,9 +180,10 @@ __global__ __launch_bounds__(KW * 64) void gemm_skinny(GemmArgs a) {
 // ---------------------------------------------------------------------------
 // streaming GEMM (row-major INT4 W, 16 < M <= 32)
 //
-// Workgroup = 8 waves; wave w owns W rows n0 + 16 w .. + 15 and the
-// workgroup covers k in [z kper, (z + 1) kper), z = blockIdx.y.  K is walked
-// in chunks of KC: the X chunk (32 rows x KC) is loaded once per workgroup,
+// Workgroup = KS groups of 8 / KS waves; wave w of a group owns W rows n0 +
+// 16 w .. + 15, the workgroup covers k in [z kper, (z + 1) kper), z =
+// blockIdx.y, and group j its j-th KS-th of that.  K is walked in chunks of
+// KC: the X chunk (32 rows x KC) is loaded once per group,
 // PD chunks ahead into registers and then into one of two LDS buffers, one
 // barrier per chunk; each wave holds PD chunks of its W rows in registers,
 // refilling a chunk's registers as soon as its MFMAs are issued.  Every load
@@ -192,25 +194,29 @@ __global__ __launch_bounds__(KW * 64) void gemm_skinny(GemmArgs a) {
 // k = 32 g + 8 i (32 consecutive codes per lane, expanded in interleaved
 // order, X permuted to match).  It reads 64 or 128 consecutive bytes of a
 // row of codes at a time, where the slab kernel reads 32: at M = 20, N x K =
-// 7168 x 28672, 50 against 62 us.
-constexpr int kStreamKW = 8, kStreamRows = 16 * kStreamKW;
+// 7168 x 28672, 50 against 62 us.  The two groups of KS = 2 are added through
+// LDS, so that 64 columns per workgroup have the waves, and the sums the
+// order, of 128 columns and twice the K ranges.
+constexpr int kStreamWaves = 8;
 
 __device__ __forceinline__ int64_t clamp_hi(int64_t v, int64_t hi) { return v < hi ? v : hi; }
 
-template <int PD, int KC, int EPI>
-__global__ __launch_bounds__(kStreamKW * 64) void gemm_stream_w4(GemmArgs a, float* part,
-                                                                 int64_t kper) {
-  constexpr int MF = 2, kThreads = kStreamKW * 64;
+template <int PD, int KC, int KS, int EPI>
+__global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_w4(GemmArgs a, float* part,
+                                                                    int64_t kper) {
+  constexpr int MF = 2, KW = kStreamWaves / KS, kThreads = KW * 64;  // of a group
   constexpr int kXLd = KC + 8;  // halves per LDS row (padding against bank conflicts)
   constexpr int kXPerThread = 16 * MF * KC / 8 / kThreads;  // 8-half pieces of an X chunk
   static_assert(kXPerThread * kThreads * 8 == 16 * MF * KC, "X pieces split evenly");
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][16 * MF * kXLd];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ __attribute__((aligned(16))) uint16_t Xs[KS][2][16 * MF * kXLd];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ks = KS == 1 ? 0 : wave / KW, kw = wave - ks * KW;
+  const int tid = threadIdx.x - ks * kThreads;
   const int r = lane & 15, g = lane >> 4;
-  const int64_t nw0 = ((int64_t)blockIdx.x * kStreamKW + wave) * 16;
-  const int64_t kbeg = (int64_t)blockIdx.y * kper;
-  const int64_t nch = kper / KC;
+  const int64_t nw0 = ((int64_t)blockIdx.x * KW + kw) * 16;
+  const int64_t kbeg = (int64_t)blockIdx.y * kper + ks * (kper / KS);
+  const int64_t nch = kper / KS / KC;
   const int64_t K = a.K;
   const int64_t wrow = clamp_hi(nw0 + r, a.N - 1);
 
@@ -247,7 +253,7 @@ __global__ __launch_bounds__(kStreamKW * 64) void gemm_stream_w4(GemmArgs a, flo
     for (int j = 0; j < kXPerThread; ++j) {
       const int e = tid + j * kThreads;
       const int row = e / (KC / 8), col = (e % (KC / 8)) * 8;
-      *reinterpret_cast<h8*>(&Xs[b][row * kXLd + col]) = interleave_h8(xr[slot][j]);
+      *reinterpret_cast<h8*>(&Xs[ks][b][row * kXLd + col]) = interleave_h8(xr[slot][j]);
     }
   };
   f4 acc[MF];
@@ -256,16 +262,22 @@ __global__ __launch_bounds__(kStreamKW * 64) void gemm_stream_w4(GemmArgs a, flo
   const auto compute = [&](const WChunk& F, int b) {
 #pragma unroll
     for (int t = 0; t < KC / 128; ++t) {
+      // (all reads of the block first: left to the compiler, each waits right
+      // before its product: M = 17, 21504 x 7168 46 us, 42 so)
+      h8 xv[4][MF];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int mf = 0; mf < MF; ++mf)
+          xv[i][mf] = *reinterpret_cast<const h8*>(
+              &Xs[ks][b][(16 * mf + r) * kXLd + 128 * t + 32 * g + 8 * i]);
       h2 s2, m2;
       scale_min_pairs(F.sm[t], s2, m2);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int kl = 128 * t + 32 * g + 8 * i;
         const h8 wv = dequant8_interleaved(F.w[t][i], s2, m2);
 #pragma unroll
-        for (int mf = 0; mf < MF; ++mf)
-          acc[mf] = mfma16(
-              wv, *reinterpret_cast<const h8*>(&Xs[b][(16 * mf + r) * kXLd + kl]), acc[mf]);
+        for (int mf = 0; mf < MF; ++mf) acc[mf] = mfma16(wv, xv[i][mf], acc[mf]);
       }
     }
   };
@@ -296,6 +308,19 @@ __global__ __launch_bounds__(kStreamKW * 64) void gemm_stream_w4(GemmArgs a, flo
     }
   }
 
+  if constexpr (KS == 2) {
+    static_assert(KW * 64 * MF * 16 <= sizeof(Xs), "the second group's sums fit");
+    f4* red = reinterpret_cast<f4*>(&Xs[0][0][0]);
+    const int at = kw * 64 + lane;
+    if (ks == 1) {
+#pragma unroll
+      for (int mf = 0; mf < MF; ++mf) red[mf * kThreads + at] = acc[mf];
+    }
+    __syncthreads();
+    if (ks == 1) return;
+#pragma unroll
+    for (int mf = 0; mf < MF; ++mf) acc[mf] += red[mf * kThreads + at];
+  }
   // acc[mf] element j: W row nw0 + 4 g + j, X row 16 mf + r
 #pragma unroll
   for (int mf = 0; mf < MF; ++mf)
@@ -943,7 +968,15 @@ static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool
 // not hold the ranges that wide workgroups need, the narrow ones take over
 // (4096 x 14336, one range: fp16 M = 32 82 -> 35, M = 64 97 -> 65, INT4 M = 128
 // 120 -> 79).
-static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, int fit) {
+//
+// Row-major INT4 W at M <= 32: the streaming kernel in place of the 128-column
+// slab kernel, and, with its two groups, of the 64-column one where K is long
+// (M = 32, us with 64 columns: 16384 x 4096 20.5 -> 19.6, 16384 x 13312 61.3 ->
+// 53.3, 5120 x 8192 22.5 -> 22.0; but 8192 x 7168 22.5, 23.5 and 4096 x 11264
+// 19.6, 19.3 in one round).  Above M = 32 the slab kernel is the faster one throughout
+// (M = 33 to 128, the streaming kernel it replaced: 4096 x 4096 31 -> 12, 28672 x
+// 7168 75 -> 63, 7168 x 28672 101 -> 83).
+static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, bool packed, int fit) {
   const int mf = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
   GemmPlan p{kSlab};
   int cols;
@@ -970,8 +1003,7 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, int fit) {
     p.slab = mf == 4 ? (narrow ? kF16M64n64 : kF16M64n128) : (narrow ? kF16M128n64 : kF16M128n128);
     cols = narrow ? 64 : 128;
   }
-  if (K < 1536) return p;
-  p.splits = split_k(ceil_div(N, cols), K, 256);
+  if (K >= 1536) p.splits = split_k(ceil_div(N, cols), K, 256);
   if (p.splits > fit) {
     const int64_t narrow = ceil_div(N, !w4 && mf == 2 ? 32 : 64);
     if (narrow <= kMaxWGs) {
@@ -982,6 +1014,10 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, int fit) {
       p.splits = fit;
     }
   }
+  if (w4 && !packed &&
+      (p.slab == kW4M32n128 || (p.slab == kW4M32n64 && N > 4096 &&
+                                K >= (N > 8192 ? 4096 : 8192) && K % (256 * p.splits) == 0)))
+    p.kernel = kStreamW4;
   return p;
 }
 
@@ -1034,13 +1070,13 @@ static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4, bool pack
 static GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool packed,
                           int fit = kMaxSplits) {
   if (M <= kSkinnyMaxM) return plan_m16(M, N, K, w4, epi, packed);
-  return M <= kDecodeMaxM ? plan_decode(M, N, K, w4, fit)
+  return M <= kDecodeMaxM ? plan_decode(M, N, K, w4, packed, fit)
                           : plan_prefill(M, N, K, w4, packed, fit);
 }
 
 int64_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, bool w4) {
   if (M <= kSkinnyMaxM || N <= 0 || K <= 0 || K % 128 != 0) return 0;
-  const GemmPlan p = gemm_plan(M, N, K, w4, EPI_F32, true);  // the splits of every call
+  const GemmPlan p = gemm_plan(M, N, K, w4, EPI_F32, true);  // as many as any call's
   return p.splits > 1 ? (int64_t)p.splits * M * N * 4 : 0;
 }
 
@@ -1063,13 +1099,14 @@ static void launch_skinny(const GemmArgs& a, hipStream_t st) {
   launch((gemm_skinny<NF, 1, KW, UNR, W4, EPI, PK>), grid, dim3(KW * 64), 0, st, a);
 }
 
-template <int EPI>
+template <int KS, int EPI>
 static void launch_stream_w4(const GemmArgs& a, int S, float* ws, hipStream_t st) {
-  const dim3 grid((unsigned)ceil_div(a.N, kStreamRows), (unsigned)S), block(kStreamKW * 64);
-  if (a.K % (256 * S) == 0)
-    launch((gemm_stream_w4<2, 256, EPI>), grid, block, 0, st, a, ws, a.K / S);
+  constexpr int cols = 16 * kStreamWaves / KS;
+  const dim3 grid((unsigned)ceil_div(a.N, cols), (unsigned)S), block(kStreamWaves * 64);
+  if (a.K % (256 * KS * S) == 0)
+    launch((gemm_stream_w4<2, 256, KS, EPI>), grid, block, 0, st, a, ws, a.K / S);
   else
-    launch((gemm_stream_w4<4, 128, EPI>), grid, block, 0, st, a, ws, a.K / S);
+    launch((gemm_stream_w4<4, 128, KS, EPI>), grid, block, 0, st, a, ws, a.K / S);
 }
 
 template <bool W4, int EPI, bool PK>
@@ -1088,8 +1125,6 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
     int fit = ws == nullptr || a.M * a.N >= ((int64_t)1 << 31) ? 1 : kMaxSplits;
     while (fit > 1 && ws_bytes < (int64_t)fit * a.M * a.N * 4) fit /= 2;
     GemmPlan p = gemm_plan(a.M, a.N, a.K, W4, EPI, PK, fit);
-    // row-major INT4 at M <= 32: see gemm_stream_w4 (same K ranges)
-    if (W4 && !PK && p.kernel == kSlab && p.slab == kW4M32n128) p.kernel = kStreamW4;
     // loads straight into LDS take 16 bytes at a time: operands off that
     // alignment go through registers, in decode by the same plan
     const uintptr_t at = reinterpret_cast<uintptr_t>(a.X) |
@@ -1111,7 +1146,12 @@ static pipo_status launch_epi(const GemmArgs& a, float* ws, int64_t ws_bytes, hi
         (W4 ? launch_slab_w4 : launch_slab_f16)(a, EPI, p.slab, direct, p.splits, ws, st);
         break;
       case kStreamW4:
-        if constexpr (W4 && !PK) launch_stream_w4<EPI>(a, p.splits, ws, st);
+        if constexpr (W4 && !PK) {
+          if (p.slab == kW4M32n128)
+            launch_stream_w4<1, EPI>(a, p.splits, ws, st);
+          else
+            launch_stream_w4<2, EPI>(a, p.splits, ws, st);
+        }
         break;
       case kBig: {
         const int64_t per_xcd = ceil_div(ceil_div(a.M, kBM) * ceil_div(a.N, kBN), kXcds);

@@ -142,3 +142,19 @@ def test_gemm_unaligned_decode_exact(M, N, K, w4):
                      dO.ptr, M, N, K, B.PIPO_EPI_F32, dWs.ptr if nbytes else None, nbytes)
                 B.pipo_dev_synchronize()
                 assert np.array_equal(dO.to_array(np.float32, (M, N)).astype(np.float64), want)
+
+
+# both sides of the rules that choose the kernel from K and the number of
+# workgroups: the streaming kernel's two groups, with chunks of 256 and of 128 k
+RULES = [(17, 8208, 4096), (31, 8208, 4352), (20, 8199, 3968), (32, 4112, 8192), (20, 4112, 8704)]
+
+
+@pytest.mark.parametrize("M,N,K", RULES)
+@pytest.mark.parametrize("w4", [False, True])
+def test_gemm_rule_edges_exact(M, N, K, w4):
+    X, W, q, want = _case(M, N, K, w4)
+    for frag in (False, True) if N % 16 == 0 else (False,):
+        for ws in (True, False):
+            print(f"gemm rules M={M} N={N} K={K} w4={w4} frag={frag} workspace={ws}", flush=True)
+            got = run_gemm(X, W, None, B.PIPO_EPI_F32, w4=q, workspace=ws, frag=frag)
+            assert np.array_equal(got.astype(np.float64), want)
