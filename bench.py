@@ -95,12 +95,16 @@ def gemm_symbols(M, N, K, epi, w4, frag):
     if M <= 16:
         cfg = None
         if epi != 5 and not (w4 and epi == 0):   # (always the skinny kernel)
-            if not w4 and not frag:
-                cfg = ((1, 1, 1, 8, 3) if N < 5120 else
-                       (1, 2, 1, 8, 2) if N <= 8192 else (1, 2, 2, 4, 2))
-            elif 5120 <= N <= 8192 and (M > 8 or (not w4 and K >= 16384)):
-                cfg = (1, 2, 1, 8, 4) if w4 else (1, 2, 1, 8, 2)
-            elif N < 5120 and M > 8 and not w4:
+            if w4:
+                if 5120 <= N <= 8192 and M > 8 and K >= 3072:
+                    cfg = (1, 2, 1, 8, 4)
+            elif not frag:
+                if N > 4096 or K > 1536:
+                    cfg = ((1, 1, 1, 8, 3) if N <= 4096 else
+                           (1, 2, 1, 8, 2) if N <= 8192 else (1, 2, 2, 4, 2))
+            elif 4096 < N <= 8192 and K >= (2560 if M > 8 else 16384):
+                cfg = (1, 2, 1, 8, 2)
+            elif N <= 4096 and M > 8 and K >= 3072:
                 cfg = (1, 1, 1, 8, 3)
         if cfg is None:
             nf = 4 if N >= 64 * 192 or epi == 5 else 1

@@ -927,31 +927,39 @@ enum { kW4M16n32 = 0, kW4M32n64, kW4M32n128, kW4M64n64, kW4M64n128, kW4M128n64, 
 
 // M <= 16.  The skinny kernel has no LDS staging and no barrier, and its 16
 // or 64 rows per workgroup fill the chip at many N; what it lacks is the
-// balance at N of 5120 to 8192, where 320 to 512 workgroups of 16 rows leave
+// balance at N of 4096 to 8192, where 257 to 512 workgroups of 16 rows leave
 // a second round half empty and X is read by each: there 32-row slab
-// workgroups (at most 256) take over, K split over their waves.  M = 16: fp16
-// 7168 x 28672 82.9 -> 61.8, 6144 x 4096 14.4 -> 11.1, INT4 63.2 -> 35.7 and
-// 11.4 -> 8.5; at M <= 8 the two are equal (17.6 against 17.9) but for fp16
-// and long K (M = 1, 5120 x 20480: 41.0 -> 34.6).  Below, 16-row slab
-// workgroups for fp16 (M = 16, 4096 x 14336: 23.3 -> 22.0; INT4 fragments
-// come in pairs, 32 rows, which would leave half the CUs idle).  With fp16 W
-// both kernels give the same bits; with INT4 W an EPI_F16 output stays with
-// the skinny kernel: EPI_SWIGLU, which only that kernel has, gives the values
-// of EPI_F16 and the SwiGLU kernel bit for bit.
+// workgroups (at most 256) take over, K split over their waves, once the K
+// range of a wave outlasts its first loads (M = 16: fp16 7168 x 28672 82.9 ->
+// 61.8, 6144 x 4096 14.4 -> 11.1; M = 12, 8192 x 2048 8.0 and 8.6; INT4 63.2 ->
+// 35.7 and 11.4 -> 8.5, but M = 12, 6912 x 2304 6.7 and 7.0); at M <= 8 the two
+// are equal (17.6 against 17.9) but for fp16 and long K (M = 1, 5120 x 20480:
+// 41.0 -> 34.6).  Up to N = 4096, 16-row slab workgroups for fp16 (M = 16, 4096 x
+// 14336: 23.3 -> 22.0, x 3072 7.6 -> 7.2, but x 2048 5.7 and 6.1; at N = 4608, a
+// second round of them, x 1536 6.9 and 8.6; INT4 fragments come in pairs, 32
+// rows, which would leave half the CUs idle).
+// With fp16 W both kernels give the same bits; with INT4 W an EPI_F16 output
+// stays with the skinny kernel: EPI_SWIGLU, which only that kernel has, gives
+// the values of EPI_F16 and the SwiGLU kernel bit for bit.
 // Row-major fp16 W: the skinny kernel's loads take 64 bytes of each of 16
 // rows, half of every 128-byte line, the slab kernel's whole lines, so it is
 // the faster one at every M and N (M = 16: 128256 x 4096 224 -> 188, 50272 x
 // 7168 182 -> 126; M = 1: 5120 x 5120 19.2 -> 11.9, 4096 x 14336 26 -> 21), with
-// 64 columns above N = 8192.
+// 64 columns above N = 8192, 32 above 4096 (M = 16, 4608 x 1024 5.3, with 16
+// 7.0); but where there is little to read (N up to 4096, K up to 1536: M = 1,
+// 4096 x 1536 5.0 and 5.3).
 static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool packed) {
   if (w4 && epi == EPI_F16) return {kSkinny};
   if (!w4 && !packed) {
-    return {kSlab, N < 5120 ? kF16M16n16 : (N <= 8192 ? kF16M16n32 : kF16M16n64)};
+    if (N <= 4096) return K <= 1536 ? GemmPlan{kSkinny} : GemmPlan{kSlab, kF16M16n16};
+    return {kSlab, N <= 8192 ? kF16M16n32 : kF16M16n64};
   }
-  const bool rows16 = M > 8, longk = !w4 && K >= 16384;
-  if (N >= 5120 && N <= 8192 && (rows16 || longk))
-    return {kSlab, w4 ? kW4M16n32 : kF16M16n32};
-  if (N < 5120 && rows16 && !w4) return {kSlab, kF16M16n16};
+  const bool rows16 = M > 8;
+  if (w4)
+    return rows16 && N >= 5120 && N <= 8192 && K >= 3072 ? GemmPlan{kSlab, kW4M16n32}
+                                                         : GemmPlan{kSkinny};
+  if (N > 4096 && N <= 8192 && (rows16 ? K >= 2560 : K >= 16384)) return {kSlab, kF16M16n32};
+  if (N <= 4096 && rows16 && K >= 3072) return {kSlab, kF16M16n16};
   return {kSkinny};
 }
 
