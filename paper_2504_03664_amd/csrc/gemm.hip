@@ -19,9 +19,10 @@
 //     128 x 64 fed by global -> LDS loads through rings of LDS stages; INT4
 //     codes reach LDS the same way and are expanded there, once per tile;
 //     fp16 may split K like gemm_slab.
-//   * gemm_tiled (prefill with operands that are not 16-byte aligned, or fp16
-//     with few big tiles that cannot be split): 128 x 128 output tiles, K staged through registers into double-buffered LDS in
-//     steps of 64, 4 waves of 64 x 64; tiles ordered per XCD so that each
+//   * gemm_tiled (prefill with operands that are not 16-byte aligned, and fp16
+//     with one to two tiles of 128 x 128 per CU and little K or row-major W):
+//     128 x 128 output tiles, K staged through registers into double-buffered
+//     LDS in steps of 64, 4 waves of 64 x 64; tiles ordered per XCD so that each
 //     XCD's L2 serves a compact block.
 // The decode kernels read each weight once per pass and do so with
 // non-temporal loads.
@@ -397,8 +398,8 @@ void launch_combine(const GemmArgs& a, int epi, const float* ws, int S, hipStrea
 }
 
 // ---------------------------------------------------------------------------
-// tiled GEMM (prefill with operands off 16-byte alignment, and fp16 prefill with
-// few big tiles that cannot be split: see plan_prefill)
+// tiled GEMM (prefill with operands off 16-byte alignment, and fp16 prefill
+// with one to two of its tiles per CU: see plan_prefill)
 constexpr int kTBM = 128, kTBN = 128, kTBK = 64, kTPad = 8;
 constexpr int kTThreads = 256;  // 2 x 2 waves of 64 x 64
 constexpr int kTGroupM = 4;
@@ -1040,16 +1041,26 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, bool packe
 // 128 x 128 slab tiles where even 8 ranges give few workgroups (M = 200,
 // 768 x 3072: 46 -> 15).
 //
+// fp16 K ranges pay while the products saved outlast the partial sums' traffic
+// (8 S M N bytes) and the merge, that is from K = 12 per workgroup on (S = 2: 72
+// big tiles, K = 1536 33.5 against 35.1 unsplit, 2048 37.9, 43.4; 96, 2048 43.0,
+// 43.7; 128, 2048 52.5, 45.7 and 4096 77, 80; S = 4 against 2: 64 tiles, 2048
+// 40.8, 37.2, 4096 52, 55), 16 with row-major W, whose unsplit alternative is
+// the faster one.  Below that, 128 x 128 slab tiles unsplit while they are half
+// a chip to one (K = 2048: M = 1024, 4096 columns 27 against 42 with four
+// ranges; 3072 38, 48; 4096 47, 54, but 6144 69, 69), and between one tile of
+// 128 x 128 per CU and two, gemm_tiled, which keeps two workgroups on a CU, where
+// the start counts (M = 1500, 3072 x 768 20.6 against 22.3, x 1024 25.1, 26.3, x
+// 2048 43.4, 43.4) and where W is row-major, 64 bytes of a row per load of the
+// big tiles (M = 384, 20480 x 5120 108 against 137; M = 1500, 3072 x 2048 43, 52).
+//
 // The ranges are those that fit the workspace.  Where the ones that a wide
 // tile needs do not, 128 x 128 slab tiles take its place while they are at
 // most kMaxWGs (4096 x 14336, one range: fp16 M = 509 254 -> 141, INT4 194 ->
 // 121; 128 x 128 tiles through registers, gemm_tiled, take 229 and 326);
 // fragment-ordered fp16 keeps the big ones if the ranges that fit give 80
 // workgroups (5120 x 20480, two ranges: M = 400, 80, 190 against 199; M = 768,
-// 120, 199 against 212).  Above kMaxWGs, fp16 big tiles that cannot be split and are half a chip or less
-// (M = 1500, 4096 x 14336: 251 against 270 with gemm_tiled) lose to gemm_tiled
-// where their start counts (K under 1024: M = 1500, 3072 x 768 21.5 against
-// 20.5) and where W is row-major, 64 bytes of a row per load (337 against 259).
+// 120, 199 against 212).
 // Outputs of fewer than 512 columns stay unsplit: the workspace query answers
 // 0 for them, as callers that size their buffers by it have seen (M = 150,
 // 384 x 1536: 19 us where four ranges would take 11; 26 with gemm_tiled).
@@ -1064,14 +1075,19 @@ static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4, bool pack
       return {kSlab, kW4M128n128, split_k(t128, K, kper, fit)};
     return {kSlab, kW4M128n256, split_k(t256, K, kper, fit)};
   }
-  const int S = split_k(big, K, kper);
-  if (big * S > 64) {
-    const int s = S < fit ? S : fit;
-    if (s == S ? S > 1 || big > 128 : packed && s > 1 && big * s >= 80) return {kBig, 0, s};
-    if (t128 > kMaxWGs)
-      return big * s <= 128 && (!packed || K < 1024) ? GemmPlan{kTiled} : GemmPlan{kBig, 0, s};
+  int S = split_k(big, K, kper);
+  while (S > 1 && K < (packed ? 12 : 17) * big * S) S /= 2;
+  const int s = S < fit ? S : fit;
+  if (t128 > kMaxWGs) {
+    const bool tiled = t128 <= 2 * kMaxWGs && (packed ? K <= 1024 : s == 1);
+    return tiled ? GemmPlan{kTiled} : GemmPlan{kBig, 0, s};
   }
-  return {kSlab, kF16M128n128, split_k(t128, K, kper, fit)};
+  if (big * S > 64 && s > 1 && (s == S || (packed && big * s >= 80)) &&
+      K > (2 * t128 > kMaxWGs ? 3072 : 2048))
+    return {kBig, 0, s};
+  int n = split_k(t128, K, kper, fit);
+  while (n > 1 && K < 8 * t128 * n) n /= 2;
+  return {kSlab, kF16M128n128, n};
 }
 
 // fit: the most K ranges the workspace has room for
