@@ -1035,7 +1035,9 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, bool packe
 // (us at M = 512: 4096 x 14336 301 with 128 x 128 tiles -> 72, 28672 x 4096,
 // 224 big tiles, 227 -> 129; M = 2048, 4096 x 4096, 128 big tiles: 104 big,
 // 70 slab); 128 columns while one K range gives at most kMaxWGs workgroups,
-// else 256.  Their two K groups sum in another order than the big tiles; K
+// else 256 while those do; beyond, big tiles are one round where these are two
+// (M = 2048, 5120 x 4096: 99 against 128; row-major, M = 4096, 2304 x 768, 44 and
+// 30, with 128 x 128 tiles through registers 40).  Their two K groups sum in another order than the big tiles; K
 // under 512 (four chunks a group) stays with one group.  fp16: big tiles with
 // K ranges (M = 512, 4096 x 14336: 202 -> 71; 28672 x 4096 202 -> 104), and
 // 128 x 128 slab tiles where even 8 ranges give few workgroups (M = 200,
@@ -1069,7 +1071,7 @@ static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4, bool pack
   const int64_t t128 = mt * ceil_div(N, 128), t256 = mt * ceil_div(N, 256);
   const int64_t kper = N < 512 ? K : 512;
   if (w4) {
-    if (big >= 192) return {kBig};
+    if (big >= 192 || t256 > kMaxWGs) return {kBig};
     if (K < 512) return {kSlab, kW4M128n256k1};
     if (t128 <= kMaxWGs && (K < 8192 || split_k(t256, K, kper) > fit))
       return {kSlab, kW4M128n128, split_k(t128, K, kper, fit)};

@@ -147,12 +147,13 @@ def test_gemm_unaligned_decode_exact(M, N, K, w4):
 # both sides of the rules that choose the kernel from K and the number of
 # workgroups: the streaming kernel's two groups, with chunks of 256 and of 128
 # k; skinny or slab at M <= 16; K ranges of big and of 128 x 128 tiles, and
-# tiles of 128 x 128 through registers
+# tiles of 128 x 128 through registers; big INT4 tiles
 RULES = [(17, 8208, 4096), (31, 8208, 4352), (20, 8199, 3968), (32, 4112, 8192), (20, 4112, 8704),
          (12, 4112, 2432), (9, 4112, 2560), (16, 4096, 3072), (3, 4096, 1536), (3, 4081, 1664),
          (16, 5136, 3072), (16, 5136, 2944),
          (300, 4112, 1024), (600, 4112, 2048), (600, 4112, 3200), (130, 1040, 2048),
-         (1030, 4112, 128), (1030, 4112, 1152), (1030, 4112, 2560)]
+         (1030, 4112, 128), (1030, 4112, 1152), (1030, 4112, 2560),
+         (1030, 7424, 256)]
 
 
 @pytest.mark.parametrize("M,N,K", RULES)
