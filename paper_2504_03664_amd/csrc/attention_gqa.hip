@@ -15,8 +15,8 @@
 // - hi)), each with a sum of its own, put together as hi + 2^-11 lo at the
 // end.  That keeps 22 bits of every p down to 2^-29 of the largest one so far
 // (20 below its score) and 11, those of the output, down to 2^-40; what it
-// drops of smaller ones is under 2^-51 each.  Waves are merged in order
-// through LDS, splits by attn_decode_combine.
+// drops of smaller ones is under 2^-51 each.  Waves are merged in
+// pairs through LDS, splits in order by attn_decode_combine.
 //
 // Bound by HBM and the fixed cost of a launch.  The kernel it replaced did
 // the G dot products and accumulator updates on the vector units, about 150
@@ -265,13 +265,22 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2))) voi
     float M = wm[0][j];
 #pragma unroll
     for (int w = 1; w < W; ++w) M = fmaxf(M, wm[w][j]);
-    float L = 0.f, A = 0.f;
+    float l[W], acc[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) {  // a wave may have no key (its maximum -inf)
       const float a = __builtin_amdgcn_exp2f((wm[w][j] - M) * kLog2e);
-      L += wl[w][j] * a;
-      A += reinterpret_cast<const float*>(lds + w * (2 * BLK))[c] * a;
+      l[w] = wl[w][j] * a;
+      acc[w] = reinterpret_cast<const float*>(lds + w * (2 * BLK))[c] * a;
     }
+#pragma unroll
+    for (int n = W / 2; n >= 1; n /= 2)  // in pairs: log2(W) roundings of a sum
+#pragma unroll
+      for (int w = 0; w < n; ++w) {
+        l[w] += l[w + n];
+        acc[w] += acc[w + n];
+      }
+    const float L = l[0];
+    float A = acc[0];
     A *= 1.f / kPScale;
     if (S == 1) {
       o[(int64_t)bi * d + (int64_t)h * D + cc] = f2h(A / L);
