@@ -98,8 +98,9 @@ def test_null_weights_rejected():
 
 
 def test_gemm_workspace_sizes():
-    """GEMM K splits (host-side planning only, no GPU needed) happen only for
-    16 < M <= 128 and stay within the cap of 8."""
+    """GEMM K splits (host-side planning only, no GPU needed): none at M <= 16
+    nor, above 128 rows, for outputs of fewer than 512 columns; otherwise 2, 4
+    or 8 where they fill the chip, in prefill too."""
     for M in (1, 16, 129, 4096):
         assert B.pipo_op_gemm_workspace_bytes(M, 100, 4096, B.PIPO_W_FP16) == 0
     for wfmt in (B.PIPO_W_FP16, B.PIPO_W_INT4_G64):
@@ -107,6 +108,12 @@ def test_gemm_workspace_sizes():
             ws = B.pipo_op_gemm_workspace_bytes(M, N, K, wfmt)
             assert ws % (M * N * 4) == 0 and ws // (M * N * 4) in (0, 2, 4, 8)
         assert B.pipo_op_gemm_workspace_bytes(17, 130, 4096, wfmt) == 8 * 17 * 130 * 4
+        for M, N, K in ((129, 528, 8192), (509, 4096, 14336), (600, 5120, 20480), (1000, 7168, 7168),
+                        (2048, 4096, 1024), (32768, 7168, 7168)):
+            ws = B.pipo_op_gemm_workspace_bytes(M, N, K, wfmt)
+            want = (2, 4, 8) if M <= 600 else (0, 2)
+            assert ws % (M * N * 4) == 0 and ws // (M * N * 4) in want
+            assert ws <= 64 << 20
 
 
 def test_disk_probe_runs_without_a_gpu(tmp_path):

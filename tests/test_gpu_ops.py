@@ -12,16 +12,15 @@ pytestmark = pytest.mark.gpu
 
 GEMM_SHAPES = [(1, 50, 128), (4, 100, 256), (16, 64, 128), (33, 130, 384), (64, 96, 128),
                (65, 200, 256), (128, 128, 128), (300, 257, 512),
-               # big tiles (at least 512 tiles of 256 x 256), ragged M and N
+               # big tiles (585 of 256 x 256), ragged M and N
                (2050, 16400, 128),
                # 64-row workgroups (N >= 12288), ragged N
                (16, 12300, 256), (40, 12288, 128), (64, 12350, 128), (7, 1000, 1024),
-               # streaming kernel: K split over workgroups (up to 8 ways), INT4
-               # chunk length not dividing K, ragged M and N
+               # slab kernel: K split over workgroups (up to 8 ways), K of an odd
+               # number of 128-k chunks, ragged M and N
                (17, 130, 4096), (32, 200, 2048), (50, 1000, 1280), (100, 300, 640),
                (128, 1030, 1024), (129, 64, 256),
-               # fp16 streaming grid of 129..191 eight-wave workgroups unsplit:
-               # six waves per workgroup, ragged N
+               # 96 columns per workgroup, ragged N
                (64, 18440, 128)]
 EPIS = [B.PIPO_EPI_F16, B.PIPO_EPI_RELU_F16, B.PIPO_EPI_ADD_F32, B.PIPO_EPI_F32]
 
@@ -132,7 +131,7 @@ def test_gemm_random_vs_oracle_definition(M, N, K):
                                    (2048, 16384, 384)])
 @pytest.mark.parametrize("w4", [False, True])
 def test_gemm_fragment_order_equals_row_major(M, N, K, w4):
-    """W in fragment order (skinny, streaming with K splits, tiled and
+    """W in fragment order (skinny, slab with K splits, tiled and
     big-tile kernels): the same products in the same order, bit for bit.
     With fp16 W at big-tile shapes the two sides are different kernels
     (global -> LDS loads against the 128 x 128 tiles)."""
@@ -153,9 +152,9 @@ def test_gemm_fragment_order_equals_row_major(M, N, K, w4):
 @pytest.mark.parametrize("frag", [False, True])
 def test_gemm_big_tiles_equal_tiled(w4, frag):
     """At M = 2050, N = 16400 (585 tiles of 256 x 256) the big-tile kernels
-    run; the first 300 rows alone (130 tiles) run on the 128 x 128 kernel.
-    Both sum every output over the same k blocks in the same order: the
-    same bits."""
+    run; the first 300 rows alone (130 tiles) run on tiles of 128 x 128 through
+    registers, with INT4 W on 128 x 256 slab tiles with one K group.  All sum
+    every output over the same k blocks in the same order: the same bits."""
     log(f"gemm big vs tiled w4={w4} frag={frag}")
     rng = np.random.default_rng(11 + w4 + 2 * frag)
     M, N, K = 2050, 16400, 256
