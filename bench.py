@@ -131,9 +131,9 @@ def gemm_symbols(M, N, K, epi, w4, frag):
     syms = [f"gemm_slab<{args}, {b}, {epi}, {pk}, true>(GemmArgs, float*, long)"]
     if w4 and not frag and 16 < M <= 32:    # row-major INT4: the streaming kernel
         wide = cfg == (2, 2, 4, 4, 2)
-        if wide or (N > 4096 and K >= (4096 if N > 8192 else 8192) and K % (256 * S) == 0):
+        if wide or (N > 4096 and K >= (2048 if N > 8192 else 4096) and K % (256 * S) == 0):
             ks = 1 if wide else 2
-            pd, kc = (2, 256) if K % (256 * ks * S) == 0 else (4, 128)
+            pd, kc = ((4, 256) if ks == 2 else (2, 256) if K % (256 * S) == 0 else (4, 128))
             syms = [f"gemm_stream_w4<{pd}, {kc}, {ks}, {epi}>(GemmArgs, float*, long)"]
     if S > 1:
         # four columns per thread when N allows (the engine's partials are aligned)

@@ -54,7 +54,7 @@ enum { PIPO_EPI_F16 = 0, PIPO_EPI_RELU_F16 = 1, PIPO_EPI_ADD_F32 = 2, PIPO_EPI_F
  * fit, or unsplit; the result is the same up to rounding.  Calls sharing a workspace must not
  * overlap in time.  Operands run fastest with X and the weights on 16-byte
  * boundaries and the (scale, min) pairs on 4-byte ones; any other address is
- * taken too.  For a given (M, N, K, wfmt, layout, epilogue), alignment and
+ * taken too.  For a given (M, N, K, wfmt, epilogue), alignment and
  * room in the workspace the summation order is fixed, so repeated calls give
  * the same bits.
  */
@@ -71,8 +71,9 @@ pipo_status pipo_op_gemm_w4(const uint16_t* X, const uint8_t* Wq, const uint16_t
                             void* stream);
 
 /* The same two GEMMs with W (or Wq, Wsm) in PIPO_LAYOUT_FRAGMENT order
- * (pipo.h; N % 16 == 0): same kernels, same summation order, so the result
- * equals the row-major call bit for bit. */
+ * (pipo.h; N % 16 == 0): the same products in the same summation order, so
+ * with aligned operands and the same workspace the result equals the row-major
+ * call bit for bit. */
 pipo_status pipo_op_gemm_f16_frag(const uint16_t* X, const uint16_t* W, const uint16_t* bias,
                                   void* out, int64_t M, int64_t N, int64_t K, int32_t epi,
                                   void* workspace, int64_t workspace_bytes, void* stream);

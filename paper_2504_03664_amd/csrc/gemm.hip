@@ -13,8 +13,8 @@
 //     loads several stages ahead; K split over waves, and over workgroups
 //     whose fp32 partial sums go to a workspace that gemm_combine adds up in
 //     a fixed order.
-//   * gemm_stream_w4 (16 < M <= 32, row-major INT4 W with N above 4096 and a long
-//     K, or above 16384).
+//   * gemm_stream_w4 (16 < M <= 32, row-major INT4 W with N above 4096 and K from
+//     2048 or 4096 on, or of 14336).
 //   * gemm_big_f16 / gemm_big_w4 (prefill with 256 x 256 tiles): 8 waves of
 //     128 x 64 fed by global -> LDS loads through rings of LDS stages; INT4
 //     codes reach LDS the same way and are expanded there, once per tile;
@@ -181,23 +181,24 @@ __global__ __launch_bounds__(KW * 64) void gemm_skinny(GemmArgs a) {
 // ---------------------------------------------------------------------------
 // streaming GEMM (row-major INT4 W, 16 < M <= 32)
 //
-// Workgroup = KS groups of 8 / KS waves; wave w of a group owns W rows n0 +
-// 16 w .. + 15, the workgroup covers k in [z kper, (z + 1) kper), z =
-// blockIdx.y, and group j its j-th KS-th of that.  K is walked in chunks of
-// KC: the X chunk (32 rows x KC) is loaded once per group,
-// PD chunks ahead into registers and then into one of two LDS buffers, one
-// barrier per chunk; each wave holds PD chunks of its W rows in registers,
-// refilling a chunk's registers as soon as its MFMAs are issued.  Every load
-// is unconditional (row and chunk indexes are clamped: rows past M or N are
-// computed and never stored, a clamped chunk is loaded again and not used),
-// which keeps the compiler's wait counts exact so that the prefetch really
-// stays in flight.  In a chunk, lane (r, g) feeds MFMA i with W row r at
-// k = 32 g + 8 i (32 consecutive codes per lane, expanded in interleaved
-// order, X permuted to match).  It reads 64 or 128 consecutive bytes of a
-// row of codes at a time, where the slab kernel reads 32: at M = 20, N x K =
-// 7168 x 28672, 50 against 62 us.  The two groups of KS = 2 are added through
-// LDS, so that 64 columns per workgroup have the waves, and the sums the
-// order, of 128 columns and twice the K ranges.
+// Workgroup = 8 waves: KS = 1, wave w owns W rows n0 + 16 w .. + 15; KS = 2, the
+// waves w and w + 4 share rows n0 + 16 w .. + 15, one for each half of a
+// chunk.  The workgroup covers k in [z kper, (z + 1) kper), z = blockIdx.y.  K
+// is walked in chunks of KC: the X chunk (32 rows x KC) is loaded once per
+// workgroup, PD chunks ahead into registers and then into one of two LDS
+// buffers, one barrier per chunk; each wave holds PD chunks of its W rows in
+// registers, refilling a chunk's registers as soon as its MFMAs are issued.
+// Every load is unconditional (row and chunk indexes are clamped: rows past M
+// or N are computed and never stored, a clamped chunk is loaded again and not
+// used), which keeps the compiler's wait counts exact so that the prefetch
+// really stays in flight.  Lane (r, g) reads 32 consecutive codes of 128 (64 or
+// 128 bytes of a row at a time, where the slab kernel reads 32), then the lanes
+// of a row exchange them (two swaps a word) so that each has 16 consecutive
+// codes of each 64, as a slab lane does, and every fourth 64 go to a sum of
+// their own: the products and sums of the slab kernel in its order, so W in
+// either layout gives the same bits.  us at M = 32, with its register-staged
+// predecessor of one sum / the slab kernel / now: 16384 x 4096 22.0 / 20.5 / 18.2,
+// 21504 x 7168 46.9 / 59 / 45.9, 7168 x 28672 51 / 62 / 52.
 constexpr int kStreamWaves = 8;
 
 __device__ __forceinline__ int64_t clamp_hi(int64_t v, int64_t hi) { return v < hi ? v : hi; }
@@ -205,33 +206,34 @@ __device__ __forceinline__ int64_t clamp_hi(int64_t v, int64_t hi) { return v < 
 template <int PD, int KC, int KS, int EPI>
 __global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_w4(GemmArgs a, float* part,
                                                                     int64_t kper) {
-  constexpr int MF = 2, KW = kStreamWaves / KS, kThreads = KW * 64;  // of a group
+  constexpr int MF = 2, KW = kStreamWaves / KS, kThreads = kStreamWaves * 64;
+  constexpr int T = KC / 128 / KS;  // runs of 128 k of a chunk that a wave takes
+  constexpr int kSums = 4 / KS;     // of a wave
+  static_assert(T >= 1 && (T * 2 >= kSums || PD % 2 == 0), "a run's sums are known");
   constexpr int kXLd = KC + 8;  // halves per LDS row (padding against bank conflicts)
   constexpr int kXPerThread = 16 * MF * KC / 8 / kThreads;  // 8-half pieces of an X chunk
   static_assert(kXPerThread * kThreads * 8 == 16 * MF * KC, "X pieces split evenly");
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[KS][2][16 * MF * kXLd];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][16 * MF * kXLd];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = KS == 1 ? 0 : wave / KW, kw = wave - ks * KW;
-  const int tid = threadIdx.x - ks * kThreads;
   const int r = lane & 15, g = lane >> 4;
   const int64_t nw0 = ((int64_t)blockIdx.x * KW + kw) * 16;
-  const int64_t kbeg = (int64_t)blockIdx.y * kper + ks * (kper / KS);
-  const int64_t nch = kper / KS / KC;
+  const int64_t kbeg = (int64_t)blockIdx.y * kper;
+  const int64_t nch = kper / KC;
   const int64_t K = a.K;
   const int64_t wrow = clamp_hi(nw0 + r, a.N - 1);
 
   struct WChunk {
-    u32x4 w[KC / 128];
-    uint32_t sm[KC / 128];
+    u32x4 w[T];
+    u32x2 sm[T];  // (scale, min) of both 64
   };
   const auto load_w = [&](WChunk& F, int64_t c) {
-    const int64_t k0 = kbeg + clamp_hi(c, nch - 1) * KC;
+    const int64_t k0 = kbeg + clamp_hi(c, nch - 1) * KC + 128 * T * ks;
 #pragma unroll
-    for (int t = 0; t < KC / 128; ++t) {
-      const int64_t kb = k0 + 128 * t + 32 * g;
-      F.w[t] = load_u32x4_stream(a.Wq + w4_byte<false>(wrow, kb, K));
-      F.sm[t] = *reinterpret_cast<const uint32_t*>(a.Wsm + w4_sm<false>(wrow, kb, K) * 2);
+    for (int t = 0; t < T; ++t) {
+      F.w[t] = load_u32x4_stream(a.Wq + w4_byte<false>(wrow, k0 + 128 * t + 32 * g, K));
+      F.sm[t] = *reinterpret_cast<const u32x2*>(a.Wsm + w4_sm<false>(wrow, k0 + 128 * t, K) * 2);
     }
   };
   // X chunks travel through registers PD chunks ahead of their use, like W:
@@ -247,38 +249,48 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_w4(GemmArgs a, 
       xr[slot][j] = load_h8(a.X + clamp_hi(row, a.M - 1) * K + k0 + col);
     }
   };
-  // X is stored already permuted to the codes' interleaved order (once per
-  // workgroup rather than once per wave and use)
   const auto store_x = [&](int b, int slot) {
 #pragma unroll
     for (int j = 0; j < kXPerThread; ++j) {
       const int e = tid + j * kThreads;
       const int row = e / (KC / 8), col = (e % (KC / 8)) * 8;
-      *reinterpret_cast<h8*>(&Xs[ks][b][row * kXLd + col]) = interleave_h8(xr[slot][j]);
+      *reinterpret_cast<h8*>(&Xs[b][row * kXLd + col]) = xr[slot][j];
     }
   };
-  f4 acc[MF];
+  f4 acc[kSums][MF];
 #pragma unroll
-  for (int mf = 0; mf < MF; ++mf) acc[mf] = f4{0.f, 0.f, 0.f, 0.f};
-  const auto compute = [&](const WChunk& F, int b) {
+  for (int u = 0; u < kSums; ++u)
 #pragma unroll
-    for (int t = 0; t < KC / 128; ++t) {
-      // (all reads of the block first: left to the compiler, each waits right
-      // before its product: M = 17, 21504 x 7168 46 us, 42 so)
+    for (int mf = 0; mf < MF; ++mf) acc[u][mf] = f4{0.f, 0.f, 0.f, 0.f};
+  // odd: whether the chunk's number is
+  const auto compute = [&](const WChunk& F, int b, int odd) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      // (all reads of the run first: left to the compiler, each waits right
+      // before its product, 46 us where it takes 42 so at M = 17, 21504 x 7168)
       h8 xv[4][MF];
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int mf = 0; mf < MF; ++mf)
           xv[i][mf] = *reinterpret_cast<const h8*>(
-              &Xs[ks][b][(16 * mf + r) * kXLd + 128 * t + 32 * g + 8 * i]);
-      h2 s2, m2;
-      scale_min_pairs(F.sm[t], s2, m2);
+              &Xs[b][(16 * mf + r) * kXLd + 128 * (T * ks + t) + 64 * (i >> 1) + 16 * g + 8 * (i & 1)]);
+      uint32_t w[4];  // 64 i / 2, word i % 2
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const auto p = __builtin_amdgcn_permlane16_swap(F.w[t][i], F.w[t][2 + i], false, false);
+        const auto q = __builtin_amdgcn_permlane32_swap(p[0], p[1], false, false);
+        w[i] = q[0];
+        w[2 + i] = q[1];
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const h8 wv = dequant8_interleaved(F.w[t][i], s2, m2);
+        h2 s2, m2;
+        scale_min_pairs(F.sm[t][i >> 1], s2, m2);
+        const h8 wv = dequant8_fp8(w[i], s2, m2);
+        const int u = (2 * (T * odd + t) + (i >> 1)) % kSums;
 #pragma unroll
-        for (int mf = 0; mf < MF; ++mf) acc[mf] = mfma16(wv, xv[i][mf], acc[mf]);
+        for (int mf = 0; mf < MF; ++mf) acc[u][mf] = mfma16(wv, xv[i][mf], acc[u][mf]);
       }
     }
   };
@@ -298,7 +310,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_w4(GemmArgs a, 
 #pragma unroll
     for (int p = 0; p < PD; ++p) {
       const int64_t c = c0 + p;
-      if (c < nch) compute(F[p], (int)(c & 1));
+      if (c < nch) compute(F[p], (int)(c & 1), p & 1);
       load_w(F[p], c + PD);
       __builtin_amdgcn_sched_barrier(0);
       // buffer (c + 1) & 1 was last read in chunk c - 1, before the barrier
@@ -309,29 +321,44 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_w4(GemmArgs a, 
     }
   }
 
+  // the sums in order; those of the second halves through LDS
+  f4 sum[MF];
+#pragma unroll
+  for (int mf = 0; mf < MF; ++mf) {
+    sum[mf] = acc[0][mf];
+    if constexpr (KS == 1) {
+#pragma unroll
+      for (int u = 1; u < kSums; ++u) sum[mf] += acc[u][mf];
+    }
+  }
   if constexpr (KS == 2) {
-    static_assert(KW * 64 * MF * 16 <= sizeof(Xs), "the second group's sums fit");
-    f4* red = reinterpret_cast<f4*>(&Xs[0][0][0]);
-    const int at = kw * 64 + lane;
+    static_assert(KW * 64 * kSums * MF * 16 <= sizeof(Xs), "the second halves' sums fit");
+    f4* red = reinterpret_cast<f4*>(&Xs[0][0]);
     if (ks == 1) {
 #pragma unroll
-      for (int mf = 0; mf < MF; ++mf) red[mf * kThreads + at] = acc[mf];
+      for (int u = 0; u < kSums; ++u)
+#pragma unroll
+        for (int mf = 0; mf < MF; ++mf) red[((u * MF + mf) * KW + kw) * 64 + lane] = acc[u][mf];
     }
     __syncthreads();
     if (ks == 1) return;
 #pragma unroll
-    for (int mf = 0; mf < MF; ++mf) acc[mf] += red[mf * kThreads + at];
+    for (int mf = 0; mf < MF; ++mf) {
+      sum[mf] += acc[1][mf];
+#pragma unroll
+      for (int u = 0; u < kSums; ++u) sum[mf] += red[((u * MF + mf) * KW + kw) * 64 + lane];
+    }
   }
-  // acc[mf] element j: W row nw0 + 4 g + j, X row 16 mf + r
+  // sum[mf] element j: W row nw0 + 4 g + j, X row 16 mf + r
 #pragma unroll
   for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int64_t m = 16 * mf + r, n = nw0 + 4 * g + j;
       if (gridDim.y == 1) {
-        epilogue<EPI>(a, m, n, acc[mf][j]);
+        epilogue<EPI>(a, m, n, sum[mf][j]);
       } else if (m < a.M && n < a.N) {
-        part[((int64_t)blockIdx.y * a.M + m) * a.N + n] = acc[mf][j];
+        part[((int64_t)blockIdx.y * a.M + m) * a.N + n] = sum[mf][j];
       }
     }
 }
@@ -979,12 +1006,13 @@ static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool
 // 120 -> 79).
 //
 // Row-major INT4 W at M <= 32: the streaming kernel in place of the 128-column
-// slab kernel, and, with its two groups, of the 64-column one where K is long
-// (M = 32, us with 64 columns: 16384 x 4096 20.5 -> 19.6, 16384 x 13312 61.3 ->
-// 53.3, 5120 x 8192 22.5 -> 22.0; but 8192 x 7168 22.5, 23.5 and 4096 x 11264
-// 19.6, 19.3 in one round).  Above M = 32 the slab kernel is the faster one throughout
-// (M = 33 to 128, the streaming kernel it replaced: 4096 x 4096 31 -> 12, 28672 x
-// 7168 75 -> 63, 7168 x 28672 101 -> 83).
+// slab kernel, and in its 64-column form of the 64-column one where K is long
+// enough for its start (M = 32, us with the slab kernel: 16384 x 2048 12.6 -> 12.0,
+// x 13312 61 -> 48, 5120 x 4096 14.6 -> 14.2, 8192 x 8192 23.7 -> 21.7; but 8192 x
+// 3072 14.1 and 14.3) and it is not one round with many ranges (4096 x 4096 11.5
+// and 12.1).  Above M = 32 the slab kernel is the faster one throughout (M = 33 to
+// 128, the streaming kernel it replaced: 4096 x 4096 31 -> 12, 28672 x 7168 75 ->
+// 63, 7168 x 28672 101 -> 83).
 static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, bool packed, int fit) {
   const int mf = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
   GemmPlan p{kSlab};
@@ -1025,7 +1053,7 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, bool packe
   }
   if (w4 && !packed &&
       (p.slab == kW4M32n128 || (p.slab == kW4M32n64 && N > 4096 &&
-                                K >= (N > 8192 ? 4096 : 8192) && K % (256 * p.splits) == 0)))
+                                K >= (N > 8192 ? 2048 : 4096) && K % (256 * p.splits) == 0)))
     p.kernel = kStreamW4;
   return p;
 }
@@ -1044,25 +1072,23 @@ static GemmPlan plan_decode(int64_t M, int64_t N, int64_t K, bool w4, bool packe
 // 768 x 3072: 46 -> 15).
 //
 // fp16 K ranges pay while the products saved outlast the partial sums' traffic
-// (8 S M N bytes) and the merge, that is from K = 12 per workgroup on (S = 2: 72
+// (8 S M N bytes) and the merge, that is from K = 14 per workgroup on (S = 2: 72
 // big tiles, K = 1536 33.5 against 35.1 unsplit, 2048 37.9, 43.4; 96, 2048 43.0,
-// 43.7; 128, 2048 52.5, 45.7 and 4096 77, 80; S = 4 against 2: 64 tiles, 2048
-// 40.8, 37.2, 4096 52, 55), 16 with row-major W, whose unsplit alternative is
-// the faster one.  Below that, 128 x 128 slab tiles unsplit while they are half
-// a chip to one (K = 2048: M = 1024, 4096 columns 27 against 42 with four
-// ranges; 3072 38, 48; 4096 47, 54, but 6144 69, 69), and between one tile of
-// 128 x 128 per CU and two, gemm_tiled, which keeps two workgroups on a CU, where
-// the start counts (M = 1500, 3072 x 768 20.6 against 22.3, x 1024 25.1, 26.3, x
-// 2048 43.4, 43.4) and where W is row-major, 64 bytes of a row per load of the
-// big tiles (M = 384, 20480 x 5120 108 against 137; M = 1500, 3072 x 2048 43, 52).
+// 43.7; 128, 2048 52.5, 45.7, 3072 65, 62 and 4096 77, 80; S = 4 against 2: 64
+// tiles, 2048 40.8, 37.2, 4096 52, 55; with row-major W two or three us later).
+// Below that, 128 x 128 slab tiles unsplit while they are half a chip to one
+// (K = 2048: M = 1024, 4096 columns 27 against 42 with four ranges; 3072 38, 48;
+// 4096 47, 54, but 6144 69, 69), and between one tile of 128 x 128 per CU and
+// two, gemm_tiled, which keeps two workgroups on a CU, where the start counts
+// (M = 1500, 3072 x 768 20.6 against 22.3, x 1024 25.1, 26.3, x 2048 43.4, 43.4) and
+// where W is row-major, 64 bytes of a row per load of the big tiles (M = 384,
+// 20480 x 5120 108 against 137; M = 1500, 3072 x 2048 43, 52).
 //
-// The ranges are those that fit the workspace.  Where the ones that a wide
-// tile needs do not, 128 x 128 slab tiles take its place while they are at
-// most kMaxWGs (4096 x 14336, one range: fp16 M = 509 254 -> 141, INT4 194 ->
-// 121; 128 x 128 tiles through registers, gemm_tiled, take 229 and 326);
-// fragment-ordered fp16 keeps the big ones if the ranges that fit give 80
-// workgroups (5120 x 20480, two ranges: M = 400, 80, 190 against 199; M = 768,
-// 120, 199 against 212).
+// The ranges are those that fit the workspace, and the same for W in either
+// layout (one range gives the same bits in all of these kernels, so both do).
+// Where the ones that a wide tile needs do not fit, 128 x 128 slab tiles take its
+// place while they are at most kMaxWGs (4096 x 14336, one range: fp16 M = 509
+// 254 -> 141, INT4 194 -> 121; gemm_tiled takes 229 and 326).
 // Outputs of fewer than 512 columns stay unsplit: the workspace query answers
 // 0 for them, as callers that size their buffers by it have seen (M = 150,
 // 384 x 1536: 19 us where four ranges would take 11; 26 with gemm_tiled).
@@ -1078,14 +1104,13 @@ static GemmPlan plan_prefill(int64_t M, int64_t N, int64_t K, bool w4, bool pack
     return {kSlab, kW4M128n256, split_k(t256, K, kper, fit)};
   }
   int S = split_k(big, K, kper);
-  while (S > 1 && K < (packed ? 12 : 17) * big * S) S /= 2;
+  while (S > 1 && K < 14 * big * S) S /= 2;
   const int s = S < fit ? S : fit;
   if (t128 > kMaxWGs) {
     const bool tiled = t128 <= 2 * kMaxWGs && (packed ? K <= 1024 : s == 1);
     return tiled ? GemmPlan{kTiled} : GemmPlan{kBig, 0, s};
   }
-  if (big * S > 64 && s > 1 && (s == S || (packed && big * s >= 80)) &&
-      K > (2 * t128 > kMaxWGs ? 3072 : 2048))
+  if (big * S > 64 && s > 1 && s == S && K > (2 * t128 > kMaxWGs ? 3072 : 2048))
     return {kBig, 0, s};
   int n = split_k(t128, K, kper, fit);
   while (n > 1 && K < 8 * t128 * n) n /= 2;
@@ -1129,10 +1154,12 @@ template <int KS, int EPI>
 static void launch_stream_w4(const GemmArgs& a, int S, float* ws, hipStream_t st) {
   constexpr int cols = 16 * kStreamWaves / KS;
   const dim3 grid((unsigned)ceil_div(a.N, cols), (unsigned)S), block(kStreamWaves * 64);
-  if (a.K % (256 * KS * S) == 0)
-    launch((gemm_stream_w4<2, 256, KS, EPI>), grid, block, 0, st, a, ws, a.K / S);
+  if constexpr (KS == 2)
+    launch((gemm_stream_w4<4, 256, 2, EPI>), grid, block, 0, st, a, ws, a.K / S);
+  else if (a.K % (256 * S) == 0)
+    launch((gemm_stream_w4<2, 256, 1, EPI>), grid, block, 0, st, a, ws, a.K / S);
   else
-    launch((gemm_stream_w4<4, 128, KS, EPI>), grid, block, 0, st, a, ws, a.K / S);
+    launch((gemm_stream_w4<4, 128, 1, EPI>), grid, block, 0, st, a, ws, a.K / S);
 }
 
 template <bool W4, int EPI, bool PK>

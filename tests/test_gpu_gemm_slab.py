@@ -165,3 +165,45 @@ def test_gemm_rule_edges_exact(M, N, K, w4):
             print(f"gemm rules M={M} N={N} K={K} w4={w4} frag={frag} workspace={ws}", flush=True)
             got = run_gemm(X, W, None, B.PIPO_EPI_F32, w4=q, workspace=ws, frag=frag)
             assert np.array_equal(got.astype(np.float64), want)
+
+
+# (M, N, K): the layouts' kernels differ (skinny and slab, streaming and slab,
+# tiles through registers and big ones), with one K range and several
+SAME_BITS = [(1, 4112, 1664), (16, 4096, 2048), (12, 4112, 2560), (9, 12304, 256),
+             (17, 16400, 1280), (20, 16400, 384), (31, 144, 16384), (32, 144, 14464), (20, 528, 28672),
+             (32, 8208, 4096), (17, 12304, 4352), (24, 4112, 8192), (40, 4112, 8192),
+             (300, 20496, 512), (300, 12304, 1536), (600, 4112, 1024), (520, 4112, 4096),
+             (770, 4112, 3072), (300, 5136, 6144)]
+
+
+@pytest.mark.parametrize("M,N,K", SAME_BITS)
+@pytest.mark.parametrize("w4", [False, True])
+def test_gemm_layouts_same_bits(M, N, K, w4):
+    """Row-major W gives the bits of fragment order, with all of the workspace,
+    with half of it and without: random operands, whose sums show an order."""
+    rng = np.random.default_rng(M + N * 3 + K)
+    X = rng.standard_normal((M, K)).astype(np.float16)
+    wfmt = B.PIPO_W_INT4_G64 if w4 else B.PIPO_W_FP16
+    if w4:
+        q = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+        sm = np.stack([rng.uniform(0.5, 1, (N, K // 64)), rng.uniform(-9, -6, (N, K // 64))],
+                      -1).astype(np.float16)
+        mats = ((q, sm), B.pipo_pack_w4(q, sm))
+        calls = (B.pipo_op_gemm_w4, B.pipo_op_gemm_w4_frag)
+    else:
+        W = rng.standard_normal((N, K), dtype=np.float32).astype(np.float16)
+        mats = ((W,), (B.pipo_pack_f16(W),))
+        calls = (B.pipo_op_gemm_f16, B.pipo_op_gemm_f16_frag)
+    full = B.pipo_op_gemm_workspace_bytes(M, N, K, wfmt)
+    dX, dWs = DB.from_array(X), DB(max(full, 16))
+    dev = [[DB.from_array(m) for m in ms] for ms in mats]
+    dO = DB(M * N * 4)
+    for nbytes in sorted({full, full // 2, 0}):
+        print(f"gemm layouts M={M} N={N} K={K} w4={w4} workspace={nbytes} of {full}", flush=True)
+        out = []
+        for call, ops in zip(calls, dev):
+            call(dX.ptr, *[o.ptr for o in ops], None, dO.ptr, M, N, K, B.PIPO_EPI_F32,
+                 dWs.ptr if nbytes else None, nbytes)
+            B.pipo_dev_synchronize()
+            out.append(dO.to_array(np.uint32, (M, N)))
+        assert np.array_equal(*out)
