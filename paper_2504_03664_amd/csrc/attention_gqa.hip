@@ -22,9 +22,9 @@
 // the G dot products and accumulator updates on the vector units, about 150
 // instructions for 4 keys, where 32 keys now take about 170; and it needed
 // more, smaller workgroups, so more splits to merge.  us with the merge, fp16
-// (INT4): b 16, 32/8 heads of 128, 544 keys 18.3 -> 9.9 (19.9 -> 11.0); b 128,
-// 64/8 heads 109 -> 60 (4.7 TB/s); b 16, 64/8 heads, 4096 keys 105 -> 54 (114
-// -> 45); b 1, 32/8 heads, 8000 keys 30 -> 15.
+// (INT4): b 16, 32/8 heads of 128, 544 keys 18.0 -> 10.4 (19.5 -> 10.5); b 128,
+// 64/8 heads 105 -> 50 (5.7 TB/s); b 16, 64/8 heads, 2000 keys 61 -> 28.5 (65 ->
+// 26); b 1, 32/8 heads, 8000 keys 30 -> 19.
 #include "attention_common.h"
 
 namespace pipo {
