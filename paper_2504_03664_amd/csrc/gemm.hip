@@ -1004,6 +1004,14 @@ static GemmPlan plan_m16(int64_t M, int64_t N, int64_t K, bool w4, int epi, bool
 // not hold the ranges that wide workgroups need, the narrow ones take over
 // (4096 x 14336, one range: fp16 M = 32 82 -> 35, M = 64 97 -> 65, INT4 M = 128
 // 120 -> 79).
+// Where long K begins, by format and 32, 64 or 128 rows, lies between the two
+// sides of what was measured, later at N = 4096 (one round either way) than at
+// 5120 to 14336 (64 columns / 128, with their ranges; fragment order): INT4 M = 32,
+// 4096 x 13312 14.8 / 15.4, x 16384 16.6 / 16.6, 14336 x 8192 22.9 / 23.6, x 14336
+// 36.8 / 33.3; M = 64, 8192 x 12288 26.7 / 27.4, x 16384 32.6 / 31.7; M = 128, 4096 x
+// 8192 21.3 / 22.6, x 11264 25.9 / 25.8, 8192 x 4096 21.8 / 22.9, x 9216 36.3 / 33.3;
+// fp16 M = 64, 4096 x 16384 29.0 / 30.5, 14336 x 8192 43.2 / 44.2, x 16384 81.3 /
+// 76.9; M = 128, 4096 x 6144 20.9 / 21.9, 8192 x 7168 35.7 / 33.7.
 //
 // Row-major INT4 W at M <= 32: the streaming kernel in place of the 128-column
 // slab kernel, and in its 64-column form of the 64-column one where K is long
